@@ -51,38 +51,73 @@ __device__ inline void tile_coords(int tile, int64_t T, int C, int &s, int64_t &
 
 // ------------------------------------------------------------------ training
 
-// One workgroup per batch tile: the tile's reference level m (median of the
-// 256 channel means), then x = log(1 + P / m) and the labels as 0/1 floats.
-// A tile id outside the data is recorded in err and gives x = y = 0.
-__global__ void __launch_bounds__(256) cnn_gather_kernel(const float *__restrict__ power,
-                                                         const uint8_t *__restrict__ labels, int S, int64_t T,
-                                                         int C, const int32_t *__restrict__ tiles, float *x,
-                                                         float *y, uint32_t *err) {
-    __shared__ float v[W];
-    const int b = blockIdx.x, t = threadIdx.x;
+// Reference level m of each batch tile (median of its 256 channel means), then
+// x = log(1 + P / m) and the labels as 0/1 floats.  A tile id outside the data
+// is recorded in err and gives x = y = 0.
+// A batch is a few tiles, far fewer than compute units, so latency bounds this:
+// kGatherSplit workgroups share a tile; each takes the level itself (1024
+// threads, 16 rows of a column each, every load issued before the first sum;
+// one wave takes the median in registers) and writes its own rows.  16 tiles:
+// 49 us with one 256-thread workgroup per tile walking its rows twice, 20 us
+// with one of 1024 threads (the logarithms on 16 compute units), 8 us now.
+constexpr int kGatherThreads = 1024, kGatherRows = H * W / kGatherThreads, kGatherSplit = 8;
+__global__ void __launch_bounds__(kGatherThreads) cnn_gather_kernel(const float *__restrict__ power,
+                                                                    const uint8_t *__restrict__ labels, int S,
+                                                                    int64_t T, int C,
+                                                                    const int32_t *__restrict__ tiles, float *x,
+                                                                    float *y, uint32_t *err) {
+    constexpr int NG = kGatherThreads / W;           // row groups
+    constexpr int OUT = H / kGatherSplit, NO = OUT / NG;  // rows this workgroup writes, per thread
+    __shared__ float v[NG][W];
+    __shared__ float level;
+    const int b = blockIdx.x / kGatherSplit, r0 = (blockIdx.x % kGatherSplit) * OUT;
+    const int t = threadIdx.x, c = t % W, g = t / W;
     const int tile = tiles[b];
     const int64_t n_tiles = (int64_t)S * (T / H) * (C / W);
     float *xb = x + (int64_t)b * HW, *yb = y + (int64_t)b * HW;
     if (tile < 0 || tile >= n_tiles) {
         if (t == 0) atomicOr(err, 1u);
-        for (int p = t; p < HW; p += 256) xb[p] = yb[p] = 0.f;
+        for (int p = r0 * W + t; p < (r0 + OUT) * W; p += kGatherThreads) xb[p] = yb[p] = 0.f;
         return;
     }
     int s, k0;
     int64_t m0;
     tile_coords(tile, T, C, s, m0, k0);
-    const int64_t base = ((int64_t)s * T + m0) * C + k0;
+    const int64_t base = ((int64_t)s * T + m0) * C + k0 + c;
+    float p[kGatherRows], own[NO];
+    uint8_t lab[NO];
+#pragma unroll
+    for (int i = 0; i < kGatherRows; ++i) p[i] = power[base + (int64_t)(NG * i + g) * C];
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+        const int64_t o = base + (int64_t)(r0 + NG * i + g) * C;
+        own[i] = power[o];
+        lab[i] = labels ? labels[o] : 0;
+    }
     float acc = 0.f;
-    for (int r = 0; r < H; ++r) acc += power[base + (int64_t)r * C + t];
-    v[t] = acc * (1.0f / H);
+#pragma unroll
+    for (int i = 0; i < kGatherRows; ++i) acc += p[i];
+    v[g][c] = acc;
     __syncthreads();
-    block_sort(v, W);
-    const float med = 0.5f * (v[W / 2 - 1] + v[W / 2]);
-    const float lv = med > 0.f ? med : 1.f;
-    for (int r = 0; r < H; ++r) {
-        const int64_t g = base + (int64_t)r * C + t;
-        xb[r * W + t] = log1pf(power[g] / lv);
-        yb[r * W + t] = labels ? (labels[g] ? 1.f : 0.f) : 0.f;
+    if (t < 64) {
+        float m[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float sum = 0.f;
+#pragma unroll
+            for (int h = 0; h < NG; ++h) sum += v[h][4 * t + q];
+            m[q] = sum * (1.0f / H);
+        }
+        const float med = wave_median256(m, t);
+        if (t == 0) level = med > 0.f ? med : 1.f;
+    }
+    __syncthreads();
+    const float lv = level;
+#pragma unroll
+    for (int i = 0; i < NO; ++i) {
+        const int o = (r0 + NG * i + g) * W + c;
+        xb[o] = log1pf(own[i] / lv);
+        yb[o] = lab[i] ? 1.f : 0.f;
     }
 }
 
@@ -235,13 +270,30 @@ __global__ void __launch_bounds__(256) cnn_wgrad_kernel(const float *__restrict_
     }
 }
 
-// grad[e] = sum over blocks of part[blk][e], in FP64, blocks in order.
-__global__ void cnn_reduce_kernel(const float *__restrict__ part, int nparts, int E, float *grad) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= E) return;
+// grad[e] = sum over blocks of part[blk][e], in FP64 and in a fixed order: a
+// workgroup takes 16 entries, thread (l, q) the blocks q, q + 64, ... of entry
+// l, and the 64 partial sums meet in LDS.  The sum is a chain of loads, so its
+// length is what bounds it: one thread per entry walked all n blocks (119 us
+// for the 512 blocks of 16 tiles), now n / 64 of them (5 us).
+constexpr int kRedEntries = 16, kRedSlices = 64;
+__global__ void __launch_bounds__(kRedEntries *kRedSlices) cnn_reduce_kernel(const float *__restrict__ part,
+                                                                             int nparts, int E, float *grad) {
+    __shared__ double red[kRedSlices][kRedEntries];
+    const int l = threadIdx.x % kRedEntries, q = threadIdx.x / kRedEntries;
+    const int e = blockIdx.x * kRedEntries + l;
     double s = 0.0;
-    for (int k = 0; k < nparts; ++k) s += part[(int64_t)k * E + e];
-    grad[e] = (float)s;
+    if (e < E) {
+#pragma unroll 8
+        for (int k = q; k < nparts; k += kRedSlices) s += part[(int64_t)k * E + e];
+    }
+    red[q][l] = s;
+    __syncthreads();
+#pragma unroll
+    for (int h = kRedSlices / 2; h > 0; h >>= 1) {
+        if (q < h) red[q][l] += red[q + h][l];
+        __syncthreads();
+    }
+    if (q == 0 && e < E) grad[e] = (float)red[0][l];
 }
 
 // Binary cross-entropy with logits: loss terms max(z, 0) - z y + log(1 + e^-|z|)
@@ -265,11 +317,18 @@ __global__ void __launch_bounds__(256) cnn_bce_kernel(const float *__restrict__ 
     if (threadIdx.x == 0) lpart[blockIdx.x] = red[0];
 }
 
-__global__ void cnn_loss_final_kernel(const double *__restrict__ lpart, int nb, int64_t n, float *loss) {
-    if (threadIdx.x != 0) return;
+__global__ void __launch_bounds__(256) cnn_loss_final_kernel(const double *__restrict__ lpart, int nb, int64_t n,
+                                                             float *loss) {
+    __shared__ double red[256];
     double s = 0.0;
-    for (int k = 0; k < nb; ++k) s += lpart[k];
-    *loss = (float)(s / (double)n);
+    for (int k = threadIdx.x; k < nb; k += 256) s += lpart[k];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+        if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *loss = (float)(red[0] / (double)n);
 }
 
 // Adam: m = b1 m + (1 - b1) g, v = b2 v + (1 - b2) g^2,
@@ -618,7 +677,8 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
 
 hipError_t launch_cnn_gather(const float *power, const uint8_t *labels, int S, int64_t T, int C,
                              const int32_t *tiles, int n, const CnnTrainBufs &b, hipStream_t st) {
-    hipLaunchKernelGGL(cnn_gather_kernel, dim3(n), dim3(256), 0, st, power, labels, S, T, C, tiles, b.x, b.y, b.err);
+    hipLaunchKernelGGL(cnn_gather_kernel, dim3(n * kGatherSplit), dim3(kGatherThreads), 0, st, power, labels, S, T, C,
+                       tiles, b.x, b.y, b.err);
     return hipGetLastError();
 }
 
@@ -635,21 +695,24 @@ hipError_t launch_cnn_backward(const float *params, int n, const CnnTrainBufs &b
     const int64_t npx = (int64_t)n * HW;
     const int nb = (int)std::min<int64_t>(kCnnLossBlocks, (npx + 255) / 256);
     hipLaunchKernelGGL(cnn_bce_kernel, dim3(nb), dim3(256), 0, st, b.z3, b.y, npx, b.d3, b.lpart);
-    hipLaunchKernelGGL(cnn_loss_final_kernel, dim3(1), dim3(64), 0, st, b.lpart, nb, npx, loss);
+    hipLaunchKernelGGL(cnn_loss_final_kernel, dim3(1), dim3(256), 0, st, b.lpart, nb, npx, loss);
     const dim3 grid(n * kCnnBlocksPerTile), blk(256);
     const int nparts = n * kCnnBlocksPerTile;
+    auto reduce = [&](int E, float *out) {
+        hipLaunchKernelGGL(cnn_reduce_kernel, dim3((E + kRedEntries - 1) / kRedEntries),
+                           dim3(kRedEntries * kRedSlices), 0, st, b.part, nparts, E, out);
+    };
     // layer 3: weights from a2 = ReLU(z2) and dz3; dz2 = (W3^T * dz3) gated by z2 > 0
     hipLaunchKernelGGL((cnn_wgrad_kernel<16, 1, true>), grid, blk, 0, st, b.z2, b.d3, b.part);
-    hipLaunchKernelGGL(cnn_reduce_kernel, dim3(1), dim3(256), 0, st, b.part, nparts, 16 * 9 + 1, grad + kW3);
+    reduce(16 * 9 + 1, grad + kW3);
     hipLaunchKernelGGL((cnn_conv_kernel<1, 16, 2>), grid, blk, 0, st, b.d3, params + kW3, nullptr, b.z2, b.d2);
     // layer 2
     hipLaunchKernelGGL((cnn_wgrad_kernel<16, 16, true>), grid, blk, 0, st, b.z1, b.d2, b.part);
-    hipLaunchKernelGGL(cnn_reduce_kernel, dim3((kCnnGradEntries + 255) / 256), dim3(256), 0, st, b.part, nparts,
-                       kCnnGradEntries, grad + kW2);
+    reduce(kCnnGradEntries, grad + kW2);
     hipLaunchKernelGGL((cnn_conv_kernel<16, 16, 2>), grid, blk, 0, st, b.d2, params + kW2, nullptr, b.z1, b.d1);
     // layer 1
     hipLaunchKernelGGL((cnn_wgrad_kernel<1, 16, false>), grid, blk, 0, st, b.x, b.d1, b.part);
-    hipLaunchKernelGGL(cnn_reduce_kernel, dim3(1), dim3(256), 0, st, b.part, nparts, 16 * 9 + 16, grad + kW1);
+    reduce(16 * 9 + 16, grad + kW1);
     return hipGetLastError();
 }
 

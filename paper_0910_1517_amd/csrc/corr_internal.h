@@ -188,28 +188,6 @@ hipError_t launch_apply_flags(int precision, const uint8_t *flags, void *spec, u
                               int C, hipStream_t st);
 hipError_t launch_pair_counts(const uint32_t *keep, int S, int T, int C, int32_t *counts, hipStream_t st);
 
-// Ascending bitonic sort of n (power of two, <= blockDim.x) floats in LDS;
-// every thread of the block must call it.
-__device__ inline void block_sort(float *v, int n) {
-    const int t = threadIdx.x;
-    for (int k = 2; k <= n; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            if (t < n) {
-                const int p = t ^ j;
-                if (p > t) {
-                    const float a = v[t], b = v[p];
-                    const bool up = (t & k) == 0;
-                    if ((a > b) == up) {
-                        v[t] = b;
-                        v[p] = a;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
 // Ascending bitonic sort of 4 x 64 = 256 floats held by one wave, element
 // 4 lane + q in v[q]: exchanges at distance >= 4 go across lanes with
 // __shfl_xor, shorter ones stay in registers.  No barriers.
