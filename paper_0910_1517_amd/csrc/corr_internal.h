@@ -55,6 +55,7 @@ struct FLaunch {
     uint32_t *err;
     int S;
     int T;
+    int sps;  // spectra per window slot (fengine_spectra)
     int max_delay;
     int sideband;
     double fs;
@@ -130,10 +131,36 @@ constexpr int kLutSteps = 1440;
 // mode: 0 FP32 spectra, 1 INT8, 2 FP8, 3 calibration partial sums; 4..6 = the
 // first three with the phase from the table
 
+// Spectra per window slot of an F-engine launch: a power of two from `least`
+// (a whole chunk) to `most`.  A workgroup transforms the spectra of a slot one
+// after the other, so a small call at `most` leaves compute units idle (8
+// signals of 1024 512-point spectra: 32 workgroups, 56 us; 512 of them at 2
+// spectra per slot: 12 us), while a large one wants its set-up (tables, ramps)
+// spread over many spectra (30 x 4096 x 4096, FP32 spectra: 719 us at 32, 735
+// at 16, 920 at 2).  The estimate below, in spectra of one workgroup: the
+// workgroups a compute unit gets, `per_cu` side by side, each costing its slot
+// plus a set-up of `setup` spectra; a last group that is not full runs its
+// fewer workgroups faster, but not in proportion (one of two workgroups alone:
+// 0.78 of the pair's time).  It picks within 3% of the fastest of all slots for
+// 28 measured shapes (4..64 signals, 512..16384 points, 64..4096 spectra).
+inline int fengine_spectra(int S, int T, int fpar, int most, int least, int per_cu, double setup) {
+    constexpr int kCus = 256;
+    int best = most;
+    double cost = 0.0;
+    for (int sps = most; sps >= least; sps >>= 1) {
+        const int64_t wgs = S * (((int64_t)T + sps * fpar - 1) / (sps * fpar));
+        const int64_t q = (wgs + kCus - 1) / kCus, rem = q % per_cu;
+        const double groups = (double)(q / per_cu) + (rem ? 0.55 + 0.45 * (double)rem / per_cu : 0.0);
+        const double c = groups * (sps + setup);
+        if (sps == most || c < cost) {
+            cost = c;
+            best = sps;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_fengine(int log2m, int mode, const FLaunch &a, hipStream_t st);
-// geometry of the F-engine launch: spectra handled per workgroup, workgroups per signal
-int fengine_spectra_per_block(int log2m);
-int fengine_fpar(int log2m);
 // per-pass twiddle table of the Stockham passes: W_{P R}^{r k} at [pass][k][r]
 void fengine_twiddle_table(int log2m, float2 *out, size_t *count);
 
@@ -141,7 +168,6 @@ void fengine_twiddle_table(int log2m, float2 *out, size_t *count);
 // int8 samples, on the FP16 matrix cores.  Tables: afrag 2 x 64 x 64 FP16,
 // tw4 N1 x 32, twb the column-pass twiddles (count in *ntwb), wsp N1 (N1 = N/64).
 void fengine4_tables(int log2m, uint16_t *afrag, float2 *tw4, float2 *twb, size_t *ntwb, float2 *wsp);
-int fengine4_spectra_per_block(int log2m);
 hipError_t launch_fengine4(int log2m, int mode, const FLaunch &a, hipStream_t st);
 
 // 16-bit fixed-point numerics (fix16.hip)

@@ -1,8 +1,8 @@
 // fengine.hip -- F-engine of the FX correlator for gfx950.
 //
-// One workgroup owns one signal s and 16*FPAR consecutive spectra; FPAR
-// independent thread groups of L = M/8 threads (M = N/2) each transform 16
-// spectra, one at a time:
+// One workgroup owns one signal s and sps*FPAR consecutive spectra (sps 16, or
+// fewer in a small call); FPAR independent thread groups of L = M/8 threads
+// (M = N/2) each transform sps spectra, one at a time:
 //
 //  1. integer delay (section 2.1, block shift; section 2.3.2, read-pointer
 //     offset into the overlapped slice): the window m of signal s is the N
@@ -249,7 +249,8 @@ fengine_kernel(FLaunch a) {
     constexpr int BM = MODE & 3;          // 0 FP32, 1 INT8, 2 FP8, 3 calibration
     constexpr bool PL = (MODE & 4) != 0;  // phase from the 1440-step table
     constexpr int M = C::M, N = C::N, L = C::L, FPAR = C::FPAR;
-    constexpr int SPB = 16 * FPAR;  // spectra per workgroup
+    const int sps = BM == 3 ? 16 : a.sps;  // spectra per transform slot (a power of two, whole chunks)
+    const int SPB = sps * FPAR;            // spectra per workgroup
     constexpr int G = (BM == 0) ? kChunk32 : kChunk8;  // spectra per X-layout chunk
     __shared__ __attribute__((aligned(16))) uint32_t lds_in[FPAR][N / 4];
     __shared__ __attribute__((aligned(16))) float2 lds_w[FPAR][C::NBUF][C::PADM];
@@ -260,8 +261,8 @@ fengine_kernel(FLaunch a) {
     const int blk = lid / a.S;
     const int u = threadIdx.x / L;  // transform slot
     const int t = threadIdx.x % L;
-    const int m0 = blk * SPB + 16 * u;
-    const bool active = m0 < a.T;  // T is a multiple of 16
+    const int m0 = blk * SPB + sps * u;
+    const bool active = m0 < a.T;  // T is a multiple of 32
 
     float2 *b0 = &lds_w[u][0][0];
     float2 *b1 = &lds_w[u][C::NBUF - 1][0];
@@ -324,7 +325,8 @@ fengine_kernel(FLaunch a) {
         pacc[j] = 0.f;
     }
 
-    // The 16 spectra in two chunks of 8.  INT8 / FP8 up to 4096 channels: each
+    // The spectra in chunks of 8 (FP32, whose chunks are pairs, in what is left of
+    // 8 where the slot has fewer).  INT8 / FP8 up to 4096 channels: each
     // chunk as two loops of 4, the copy of the loop body for half hh (a constant
     // after unrolling) putting the codes into the chunk's first (hh = 0, spectra
     // 0..3) or second (hh = 1) pair of words; at 8192 channels and more, where
@@ -333,11 +335,11 @@ fengine_kernel(FLaunch a) {
     // eighth spectrum, outside the loop.
     constexpr int NH = ((BM == 1 || BM == 2) && LOGM <= 11) ? 2 : 1;
 #pragma unroll 1
-    for (int r8 = 0; r8 < 16; r8 += 8) {
+    for (int r8 = 0; r8 < sps; r8 += 8) {
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh) {
 #pragma unroll 1
-    for (int r = r8 + (8 / NH) * hh; r < r8 + (8 / NH) * (hh + 1); ++r) {
+    for (int r = r8 + (8 / NH) * hh; r < min(sps, r8 + (8 / NH) * (hh + 1)); ++r) {
         const int m = m0 + r;
         // all in-loop addressing derives from this opaque copy of t, so that it
         // is recomputed per spectrum instead of being hoisted and held live
@@ -409,7 +411,7 @@ fengine_kernel(FLaunch a) {
             // table mode: the table entry nearest each channel's phase, a table load too
             if constexpr (PL) ev[j] = a.lut[lut_index(c_lut, (double)(tt + L * j) * fn)];
         }
-        if (active && r < 15) fetch(m + 1);
+        if (active && r + 1 < sps) fetch(m + 1);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const float2 za = za0[padc(L * j)];
@@ -498,9 +500,11 @@ fengine_kernel(FLaunch a) {
 }
 
 template <int LOGM>
-hipError_t launch_one(int mode, const FLaunch &a, hipStream_t st) {
+hipError_t launch_one(int mode, FLaunch a, hipStream_t st) {
     using C = FCfg<LOGM>;
-    const int spb = 16 * C::FPAR;
+    // workgroups per compute unit: 16 waves' worth (the LDS of two ping-pong buffers agrees)
+    a.sps = mode == 3 ? 16 : fengine_spectra(a.S, a.T, C::FPAR, 16, (mode & 3) == 0 ? 2 : 8, 1024 / C::WG, 1.0);
+    const int spb = a.sps * C::FPAR;
     const int nblk = (a.T + spb - 1) / spb;
     const dim3 grid(a.S * nblk), block(C::WG);
     switch (mode) {
@@ -531,20 +535,6 @@ __global__ void calib_reduce_kernel(const float *part, int S, int C, int nparts,
 }
 
 }  // namespace
-
-int fengine_fpar(int log2m) {
-    switch (log2m) {
-    case 8: return FCfg<8>::FPAR;
-    case 9: return FCfg<9>::FPAR;
-    case 10: return FCfg<10>::FPAR;
-    case 11: return FCfg<11>::FPAR;
-    case 12: return FCfg<12>::FPAR;
-    case 13: return FCfg<13>::FPAR;
-    default: return 0;
-    }
-}
-
-int fengine_spectra_per_block(int log2m) { return 16 * fengine_fpar(log2m); }
 
 // Twiddles of passes 1..NPASS-1 in the order of Pass<>::TOFF: for each pass the
 // block [k < P][r < R] of W_{P R}^{r k} = exp(-2 pi i r k / (P R)), computed in

@@ -22,8 +22,8 @@
 //                       unfolded with 2 Y[j] = (U[j] + U*[N1 - j])
 //                       - i W_2N1^j (U[j] - U*[N1 - j]).
 //
-// Steps per spectrum (a workgroup owns one signal and 32 FPAR consecutive
-// spectra, FPAR windows in flight):
+// Steps per spectrum (a workgroup owns one signal and sps FPAR consecutive
+// spectra, sps 32 or fewer in a small call, FPAR windows in flight):
 //  1. the window's int8 bytes are staged in LDS (16-byte aligned loads with a
 //     byte funnel shift, prefetched one spectrum ahead);
 //  2. (*) on the matrix cores: each wave computes one 32 x 32 tile of the
@@ -87,7 +87,7 @@ struct F4Cfg {
     static constexpr int NBUF = 1;          // column passes run in place
     static constexpr int AP = 72;           // LDS row pitch (FP16) of the DFT-64 rows
     static constexpr int NSPEC = WG / 4;    // channels of column 0 per iteration (FPAR N1)
-    static constexpr int SPS = 32;          // spectra per window slot
+    static constexpr int SPS = 32;          // most spectra per window slot
 };
 
 // entries of the column-pass twiddle table: P R per pass 1..NPASS-1
@@ -311,7 +311,11 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
         if constexpr (PW == 2) reinterpret_cast<_Float16 *>(a.power)[i] = (_Float16)(p * a.power_scale);
     };
     constexpr int M = C::M, N = C::N, N1 = C::N1, L = C::L, FPAR = C::FPAR, WG = C::WG;
-    constexpr int SPS = C::SPS, SPB = SPS * FPAR;
+    constexpr int SPB_MAX = C::SPS * FPAR;
+    // spectra per window slot: a power of two, a whole number of chunks (the calibration
+    // partials are laid out for 32)
+    const int sps = BM == 3 ? C::SPS : a.sps;
+    const int SPB = sps * FPAR;
     constexpr int G = (BM == 0) ? kChunk32 : kChunk8;
     constexpr int RL = C::RLAST == 1 ? 8 : C::RLAST;  // radix of the last column pass
     constexpr int NBL = 8 / RL;                       // its butterflies per thread
@@ -329,7 +333,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     __shared__ __attribute__((aligned(16))) float2 lds_b[C::NBUF][FPAR * 32 * C::CS];
     __shared__ __attribute__((aligned(16))) uint16_t lds_a[2][64 * C::AP];  // FP16 rows (hi, lo)
     __shared__ __attribute__((aligned(16))) float2 lds_u[FPAR * N1];  // column 0 outputs
-    __shared__ float2 lds_rot[SPB];
+    __shared__ float2 lds_rot[SPB_MAX];
 
     const int tid = threadIdx.x;
     const int nblk = (a.T + SPB - 1) / SPB;
@@ -451,7 +455,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
 
     // ---- window fetch: thread t of slot t / L loads bytes 16 (t mod L) .. + 15
     const int fu = tid / L, ft = tid % L;
-    const int m_f0 = mblk + SPS * fu;  // first spectrum of this thread's fetch slot
+    const int m_f0 = mblk + sps * fu;  // first spectrum of this thread's fetch slot
     const bool f_active = m_f0 < a.T;  // T is a multiple of 32
     const uint32_t *row = reinterpret_cast<const uint32_t *>(a.x + (int64_t)s * a.row_stride);
     const uint32_t sh = (uint32_t)(D & 3);
@@ -470,7 +474,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     float2 *lb0 = &lds_b[0][0];
     float2 *lb1 = &lds_b[C::NBUF - 1][0];
     // spectra of the thread's column slot and of its column-0 channel
-    const int m_c0 = mblk + SPS * bu, m_s0 = mblk + SPS * nspec_u;
+    const int m_c0 = mblk + sps * bu, m_s0 = mblk + sps * nspec_u;
     const bool c_active = m_c0 < a.T, s_active = m_s0 < a.T;
     // chunk index of channel k (16-byte units) within a spectrum group
     auto chunk_base = [&](int k) -> uint32_t {
@@ -512,7 +516,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
                 *reinterpret_cast<uint4 *>(&lds_x[r & 1][fu][4 * ft]) = d;
             }
         }
-        if (f_active && r + 1 < SPS) fetch(m_f0 + r + 1);
+        if (f_active && r + 1 < sps) fetch(m_f0 + r + 1);
         __syncthreads();
         // 2. (*) on the matrix cores: hi and lo twiddle halves into one FP32 sum
         f4_float16 acc = {};
@@ -564,7 +568,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
         }
         // 5-6. phase, requantisation and corner turn of every channel
         const int mc = m_c0 + r;
-        const float2 rot_c = lds_rot[SPS * bu + r];
+        const float2 rot_c = lds_rot[sps * bu + r];
         const uint32_t bsel = (0x03020100u & ~(0xFFu << (8 * (r & 3)))) | (0x04u << (8 * (r & 3)));
         uint4 *gbase_c = reinterpret_cast<uint4 *>(a.spec) + (int64_t)(mc / G) * M * a.S;
         if (cp != 0) {
@@ -591,7 +595,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
             float2 X;
             X.x = fmaf(wsp.x, df.y, fmaf(wsp.y, df.x, sm.x));
             X.y = fmaf(-wsp.x, df.x, fmaf(wsp.y, df.y, sm.y));
-            const float2 rot_s = lds_rot[SPS * nspec_u + r];
+            const float2 rot_s = lds_rot[sps * nspec_u + r];
             uint4 *gbase_s = reinterpret_cast<uint4 *>(a.spec) + (int64_t)(ms / G) * M * a.S;
             // column 0 unfolds 2 X: power and the calibration sum take |X|^2 = |2 X|^2 / 4
             if constexpr (BM != 3) {
@@ -609,7 +613,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
         // half does not fit the registers; those launches keep one loop.)
         constexpr uint32_t B = BM == 1 ? kI8Bias : 0u;
 #pragma unroll 1
-        for (int r8 = 0; r8 < SPS; r8 += 8) {
+        for (int r8 = 0; r8 < sps; r8 += 8) {
 #pragma unroll 1
             for (int r = r8; r < r8 + 4; ++r) spectrum(r, std::integral_constant<int, 0>{});
 #pragma unroll 1
@@ -627,7 +631,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
         }
     } else {
 #pragma unroll 1
-        for (int r = 0; r < SPS; ++r) spectrum(r, std::integral_constant<int, -1>{});
+        for (int r = 0; r < sps; ++r) spectrum(r, std::integral_constant<int, -1>{});
     }
 
     if constexpr (BM == 3) {
@@ -650,9 +654,10 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
 }
 
 template <int LOGM>
-hipError_t launch4_one(int mode, const FLaunch &a, hipStream_t st) {
+hipError_t launch4_one(int mode, FLaunch a, hipStream_t st) {
     using C = F4Cfg<LOGM>;
-    const int spb = C::SPS * C::FPAR;
+    a.sps = mode == 3 ? C::SPS : fengine_spectra(a.S, a.T, C::FPAR, C::SPS, (mode & 3) == 0 ? 2 : 8, 3, 2.0);
+    const int spb = a.sps * C::FPAR;
     const int nblk = (a.T + spb - 1) / spb;
     const dim3 grid(a.S * nblk), block(C::WG);
     const int pw = (mode == 3 || !a.power) ? 0 : (a.power_f16 ? 2 : 1);
@@ -718,15 +723,6 @@ void fengine4_tables(int log2m, uint16_t *afrag, float2 *tw4, float2 *twb, size_
             const double b = -M_PI * (double)j / (double)N1;
             wsp[j] = make_float2((float)std::cos(b), (float)std::sin(b));
         }
-}
-
-int fengine4_spectra_per_block(int log2m) {
-    switch (log2m) {
-    case 8: return F4Cfg<8>::SPS * F4Cfg<8>::FPAR;
-    case 10: return F4Cfg<10>::SPS * F4Cfg<10>::FPAR;
-    case 11: return F4Cfg<11>::SPS * F4Cfg<11>::FPAR;
-    default: return 0;
-    }
 }
 
 hipError_t launch_fengine4(int log2m, int mode, const FLaunch &a, hipStream_t st) {
