@@ -11,7 +11,8 @@
 // directly onto 32x32 MFMA tiles whose K dimension is the time axis:
 //   INT8   v_mfma_i32_32x32x32_i8   (exact int32 sums)
 //   FP8    v_mfma_f32_32x32x16_fp8_fp8 (OCP e4m3, FP32 sums)
-//   FP32   v_mfma_f32_32x32x2_f32
+//   FP32   v_mfma_f32_32x32x16_bf16 on the three BF16 parts of each value
+//          (v_mfma_f32_32x32x2_f32 for data that are not finite; below)
 // A and B operands are loaded straight from the X layout into registers: lane
 // l holds signal 32a + (l mod 32) and the chunks of spectra picked by l / 32;
 // since A and B lanes hold the same spectra in the same byte order, the
@@ -371,13 +372,288 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
     __syncthreads();  // the LDS may be reused by the next block of a persistent loop
 }
 
+// ------------------------------------------------ FP32 on the BF16 matrix cores
+//
+// The FP32 X-engine was bound by the FP32 matrix cores (0.16 PFLOP/s, 1/16 of
+// the BF16 rate).  An FP32 number is the exact sum of three BF16 numbers (each
+// the nearest BF16 of what the ones before leave: 8 significant bits apiece, 24
+// in all), so a product of two is nine BF16 products, each exact in FP32.  The
+// three smallest, below 2^-25 of the whole, are left out; the other six go through
+// v_mfma_f32_32x32x16_bf16, which takes 16 spectra where the FP32 instruction
+// takes 2: 6/16 of the matrix time.  The sums are rounded a sixteenth as often,
+// so they are more exact: 2.3e-7 of the visibilities at 64 x 512 x 16384 before
+// (against 64 bits, the F-engine's part included), 0.8e-7 now.  The kernel took
+// 1.70 ms there, now 1.06 ms (4.1 TB/s; its loads alone 0.83 ms, its arithmetic
+// alone 0.88 ms at the 1.7 GHz this load leaves the clock).
+//
+// Values of 2^-100 and more in magnitude (and zeros) split exactly.  A value
+// that is infinite or NaN, or within half a BF16 step of the largest FP32
+// number, leaves a NaN in every sum it takes part in; a block that ends with
+// a sum that is not finite is done again on the FP32 instructions, so such data
+// give what they always gave.
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t bf16_pair(float x, float y) {  // nearest BF16 of x (low half) and y
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){x, y}, v2bf));
+}
+
+// p[i] = the i-th BF16 parts of x (low half) and y (high half)
+__device__ __forceinline__ void split_pair(float x, float y, uint32_t (&p)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        p[i] = bf16_pair(x, y);
+        if (i < 2) {
+            x -= __uint_as_float(p[i] << 16);
+            y -= __uint_as_float(p[i] & 0xFFFF0000u);
+        }
+    }
+}
+
+constexpr int kSplitChunks = 8;  // chunks of 2 spectra per K-step
+
+// The block of xengine_block, for FP32 spectra.  A K-step is 16 spectra: lanes
+// 0-31 take its first four chunks of their signal, lanes 32-63 the other four
+// (8 spectra each, the K slots of a lane).  The chunks go from global memory
+// straight into LDS (the sums, the six parts of both operands and a tile in
+// progress leave no registers to hold them), double-buffered, 64 KB per
+// compute unit in flight during a step.  Rows of 128 bytes, and the chunk of
+// channel k of signal s in place k xor (s mod 8) of its row: the lanes of a
+// DMA load choose which channel they fetch, and 8 rows of an operand read
+// cover the banks once.  A wave splits the operands of its channel after
+// reading them, once for all products, since the same registers serve as A and
+// B.  Flagged cells are zeroed before the split.
+template <int NT, bool GATED, bool MASKED>
+__device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ spec, float *out, int S, int C, int T,
+                                                    int splits, int kb, int sp, uint8_t *lds,
+                                                    const uint8_t *__restrict__ gate, int bin,
+                                                    const uint32_t *__restrict__ keep) {
+    constexpr int blk = 32 * NT * 128;  // LDS bytes of a staged chunk block
+    static_assert(2 * kSplitChunks * blk <= x_lds_bytes<NT>(), "both buffers fit");
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = kXWaves * kb + wv;
+    const int lane = threadIdx.x & 63, row = lane & 31, lg = lane >> 5;
+    const int steps = T / (2 * kSplitChunks) / splits;
+    const int64_t P = (int64_t)S * (S + 1) / 2;
+    if (steps < 1) return;
+
+    // staging: thread i fills the 16 bytes i of each chunk block
+    const int i = threadIdx.x, si = i >> 3;
+    const bool cp = si < S;
+    const uint32_t src = si * 128 + 16 * ((i & 7) ^ (si & 7));
+    const int64_t gstride = (int64_t)C * S * 16;  // bytes between chunks
+    const uint8_t *gbase = spec + (int64_t)kb * S * 128 + (int64_t)sp * steps * kSplitChunks * gstride;
+    auto stage = [&](int st, int buf) __attribute__((always_inline)) {
+        const uint8_t *g = gbase + (int64_t)st * kSplitChunks * gstride + src;
+        uint8_t *l = lds + buf * kSplitChunks * blk + wv * 1024;
+        if (cp) {
+#pragma unroll
+            for (int j = 0; j < kSplitChunks; ++j)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + j * gstride),
+                                                 (__attribute__((address_space(3))) void *)(l + j * blk), 16, 0, 0);
+        }
+    };
+    // keep bits of this lane's 8 spectra of a step, per row tile
+    uint32_t kb8[NT];
+    const uint32_t *kw = nullptr;
+    uint32_t koff[NT];
+    if constexpr (MASKED) {
+        kw = keep + (int64_t)kb * (T / 32) * S * 8;
+#pragma unroll
+        for (int a = 0; a < NT; ++a) koff[a] = min(32 * a + row, S - 1) * 8 + wv;
+    }
+    auto load_keep = [&](int st) __attribute__((always_inline)) {
+        if constexpr (MASKED) {
+            const int64_t s_ = (int64_t)sp * steps + st;
+#pragma unroll
+            for (int a = 0; a < NT; ++a) kb8[a] = (kw + (s_ >> 1) * S * 8)[koff[a]] >> (16 * (s_ & 1) + 8 * lg);
+        }
+    };
+
+    constexpr int NTILE = ntri(NT) + NT * NT;  // the R tiles (upper triangle), then the M tiles
+    v16f acc[NTILE];
+#pragma unroll
+    for (int t = 0; t < NTILE; ++t) acc[t] = v16f{0};
+
+    // rows past S stay zero, so that every operand read is unconditional
+    for (int e = i; e < 2 * kSplitChunks * (32 * NT - S) * 8; e += 64 * kXWaves) {
+        const int ch = e / ((32 * NT - S) * 8), r = e % ((32 * NT - S) * 8);
+        *reinterpret_cast<uint4 *>(lds + ch * blk + S * 128 + r * 16) = make_uint4(0, 0, 0, 0);
+    }
+    v4u re[NT][3], im[NT][3];  // operand parts; word j: spectra 2 j, 2 j + 1 of this lane's eight
+    v4u m;                     // the gate's spectra (B operands)
+    uint32_t k8[NT];
+    // operand parts of row tile a in step st; k: its keep bits
+    auto split = [&](int a, int st, uint32_t k) __attribute__((always_inline)) {
+        const uint8_t *lb = lds + ((st & 1) * kSplitChunks + 4 * lg) * blk + row * 128 + 16 * (wv ^ (row & 7));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            v4u x = *reinterpret_cast<const v4u *>(lb + j * blk + 32 * a * 128);
+            if constexpr (MASKED) {
+                const uint32_t m0 = 0u - ((k >> (2 * j)) & 1u), m1 = 0u - ((k >> (2 * j + 1)) & 1u);
+                x &= v4u{m0, m0, m1, m1};
+            }
+            uint32_t p[3], q[3];
+            split_pair(__uint_as_float(x[0]), __uint_as_float(x[2]), p);
+            split_pair(__uint_as_float(x[1]), __uint_as_float(x[3]), q);
+#pragma unroll
+            for (int h = 0; h < 3; ++h) {
+                re[a][h][j] = p[h];
+                im[a][h][j] = q[h];
+            }
+        }
+    };
+    auto load_gate = [&](int st) __attribute__((always_inline)) {
+        if constexpr (GATED) {
+            const int64_t g = 2 * kSplitChunks * ((int64_t)sp * steps + st) + 8 * lg;
+            const uint2 q = *reinterpret_cast<const uint2 *>(gate + g);
+            const uint32_t b4 = (uint32_t)bin * 0x01010101u, lo = eq_bytes(q.x, b4), hi = eq_bytes(q.y, b4);
+            m = v4u{__builtin_amdgcn_perm(0u, lo, 0x01010000u), __builtin_amdgcn_perm(0u, lo, 0x03030202u),
+                    __builtin_amdgcn_perm(0u, hi, 0x01010000u), __builtin_amdgcn_perm(0u, hi, 0x03030202u)};
+        }
+    };
+    auto mac = [&](const v4u &x, const v4u &y, v16f &d) __attribute__((always_inline)) {
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, x),
+                                                    __builtin_bit_cast(v8bf, GATED ? (v4u)(y & m) : y), d, 0, 0, 0);
+    };
+    // Tiles of the step: the products of each, the smaller ones first, go into a
+    // sum of their own, which then joins the running one (an addition into the
+    // large running sum rounds at its size, and the matrix cores round it less
+    // exactly than the vector ALUs: with one chain into it the error was 3.5
+    // times larger).  The tiles' chains alternate.
+    constexpr int NR = ntri(NT);
+    auto product = [&](auto tag, int h, bool second, v16f &d) __attribute__((always_inline)) {
+        constexpr int t = decltype(tag)::value;
+        constexpr int pi[6] = {0, 1, 2, 0, 1, 0}, pj[6] = {2, 1, 0, 1, 0, 0};
+        if constexpr (t < NR) {
+            constexpr int b = t == 0 ? 0 : 1, a = t == 2 ? 1 : 0;
+            if (second) mac(im[a][pi[h]], im[b][pj[h]], d);
+            else mac(re[a][pi[h]], re[b][pj[h]], d);
+        } else if (!second) {
+            constexpr int a = (t - NR) / NT, b = (t - NR) % NT;
+            mac(im[a][pi[h]], re[b][pj[h]], d);
+        }
+    };
+    auto tiles = [&](auto... tags) __attribute__((always_inline)) {
+        v16f d[sizeof...(tags)];
+#pragma unroll
+        for (int q = 0; q < (int)sizeof...(tags); ++q) d[q] = v16f{0};
+#pragma unroll
+        for (int h = 0; h < 6; ++h) {
+            int q = 0;
+            (product(tags, h, false, d[q++]), ...);
+            q = 0;
+            (product(tags, h, true, d[q++]), ...);
+        }
+        int q = 0;
+        ((acc[decltype(tags)::value] += d[q++]), ...);
+    };
+    // interleave n products with v vector instructions after each
+#define X_MIX(n, v)                                        \
+    _Pragma("unroll") for (int q_ = 0; q_ < (n); ++q_) {   \
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); \
+        __builtin_amdgcn_sched_group_barrier(0x002, v, 0); \
+    }
+    auto arrived = [&]() __attribute__((always_inline)) {  // this wave's loads are in LDS, then every wave's
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+    };
+    stage(0, 0);
+    load_keep(0);
+    load_gate(0);
+    arrived();
+    if constexpr (NT == 2) {
+        // The parts of row tile 0 are made a phase ahead of their use, and those of
+        // tile 1 during the products of tile 0, so that vector and matrix
+        // instructions share a wave's time (they took turns before, 33% and 43% of
+        // it).  A buffer is filled again as soon as every wave has read tile 1 from
+        // it, with the next step's loads still in flight: these alone are waited
+        // for, by count.  Past the end the last step is loaded again, unused.
+        using std::integral_constant;
+        auto clamped = [&](int st) { return st < steps ? st : steps - 1; };
+        k8[0] = MASKED ? kb8[0] : 0u;
+        k8[1] = MASKED ? kb8[1] : 0u;
+        stage(clamped(1), 1);
+        load_keep(clamped(1));
+        split(0, 0, k8[0]);
+#pragma unroll 1
+        for (int st = 0; st < steps; ++st) {
+            __builtin_amdgcn_sched_barrier(0);
+            split(1, st, k8[1]);
+            tiles(integral_constant<int, 0>{}, integral_constant<int, 3>{});
+            X_MIX(18, 6)
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (MASKED) {
+                k8[0] = kb8[0];
+                k8[1] = kb8[1];
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            stage(clamped(st + 2), st & 1);
+            load_keep(clamped(st + 2));
+            __builtin_amdgcn_sched_barrier(0);
+            tiles(integral_constant<int, 4>{}, integral_constant<int, 1>{}, integral_constant<int, 5>{});
+            X_MIX(24, 2)
+            __builtin_amdgcn_sched_barrier(0);
+            // step st + 1's chunks: all but the loads issued since (8, and the keep words;
+            // a wave without a signal of its own waits for nothing)
+            if constexpr (MASKED) asm volatile("s_waitcnt vmcnt(10)\n\ts_barrier" ::: "memory");
+            else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            split(0, st + 1, k8[0]);
+            tiles(integral_constant<int, 2>{}, integral_constant<int, 6>{});
+            X_MIX(18, 6)
+            __builtin_amdgcn_sched_barrier(0);
+            load_gate(clamped(st + 1));
+        }
+        arrived();
+    } else {
+#pragma unroll 1
+        for (int st = 0; st < steps; ++st) {
+            k8[0] = MASKED ? kb8[0] : 0u;
+            if (st + 1 < steps) {  // into the buffer that was last read a step ago
+                stage(st + 1, (st + 1) & 1);
+                load_keep(st + 1);
+            }
+            split(0, st, k8[0]);
+            tiles(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
+            load_gate(st + 1 < steps ? st + 1 : st);
+            arrived();
+        }
+    }
+#undef X_MIX
+    float z = 0.f;  // NaN if a sum is not finite
+#pragma unroll
+    for (int t = 0; t < NTILE; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) z = fmaf(acc[t][r], 0.f, z);
+    if (__syncthreads_or(z != z)) {
+        xengine_block<NT, CORR_FP32, float, GATED, MASKED>(spec, out, S, C, T, splits, kb, sp, lds, gate, bin, keep);
+        return;
+    }
+    v16f accR[ntri(NT)], accM[NT * NT];
+#pragma unroll
+    for (int t = 0; t < ntri(NT); ++t) accR[t] = acc[t];
+#pragma unroll
+    for (int t = 0; t < NT * NT; ++t) accM[t] = acc[ntri(NT) + t];
+    auto *mlds = reinterpret_cast<float(*)[32][33]>(lds + wv * NT * NT * 32 * 33 * 4);
+    x_epilogue<NT, float>(accR, accM, out + ((int64_t)sp * C + c) * P * 2, S, P, mlds);
+    __syncthreads();
+}
+
 template <int NT, int PREC, typename ACC, bool MASKED>
 __global__ void __launch_bounds__(64 * kXWaves)
 xengine_kernel(const uint8_t *__restrict__ spec, const uint32_t *__restrict__ keep, ACC *acc, int S, int C, int T,
                int splits) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[x_lds_bytes<NT>()];
-    xengine_block<NT, PREC, ACC, false, MASKED>(spec, acc, S, C, T, splits, blockIdx.x, blockIdx.y, lds, nullptr, 0,
+    if constexpr (PREC == CORR_FP32) {
+        __shared__ __attribute__((aligned(16))) uint8_t lds[x_lds_bytes<NT>()];
+        xengine_block_split<NT, false, MASKED>(spec, acc, S, C, T, splits, blockIdx.x, blockIdx.y, lds, nullptr, 0,
                                                keep);
+    } else {
+        __shared__ __attribute__((aligned(16))) uint8_t lds[x_lds_bytes<NT>()];
+        xengine_block<NT, PREC, ACC, false, MASKED>(spec, acc, S, C, T, splits, blockIdx.x, blockIdx.y, lds, nullptr,
+                                                   0, keep);
+    }
 }
 
 // Gated correlation: one workgroup per (task, bin), task = (channel block kb,
@@ -391,13 +667,18 @@ template <int NT, int PREC, typename ACC>
 __global__ void __launch_bounds__(64 * kXWaves)
 xengine_gated_kernel(const uint8_t *__restrict__ spec, const uint8_t *__restrict__ gate, ACC *acc, int64_t acc_elems,
                      int S, int C, int T, int splits, int n_bins) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[x_lds_bytes<NT>()];
+    __shared__ __attribute__((aligned(16))) uint8_t
+        lds[x_lds_bytes<NT>()];
     const int w = blockIdx.x, xcd = w & (kXcds - 1), j = w / kXcds;
     const int bin = j % n_bins, task = kXcds * (j / n_bins) + xcd;
     const int nkb = C / kXWaves;
     if (task >= nkb * splits) return;  // padding of the last group of 8 tasks
-    xengine_block<NT, PREC, ACC, true>(spec, acc + bin * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds, gate,
-                                       bin);
+    if constexpr (PREC == CORR_FP32)
+        xengine_block_split<NT, true, false>(spec, acc + bin * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds,
+                                             gate, bin, nullptr);
+    else
+        xengine_block<NT, PREC, ACC, true>(spec, acc + bin * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds,
+                                           gate, bin);
 }
 
 // One launch over the tasks of a batch of correlations of different shapes
