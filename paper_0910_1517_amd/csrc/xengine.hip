@@ -145,13 +145,23 @@ __device__ __forceinline__ uint4 keep_chunk(uint4 v, uint32_t kb8) {
 // MASKED: the flagged cells (keep bits clear; keep words [C/8][T/32][S][8],
 // bit i of word w = spectrum 32 w + i) are zeroed as the chunks are staged,
 // which is the product of zeroed spectra without writing them.
-template <int NT, int PREC, typename ACC, bool GATED = false, bool MASKED = false>
+// NB = 2 (8-bit codes, GATED): the workgroup takes half of the block's channels,
+// 4 (channel half + ...), for two bins: wave w channel w mod 4, bin + w / 4 (left
+// out at or past n_bins).  The spectra are staged once for both bins; acc_elems
+// elements apart are the bins' accumulators.
+template <int NT, int PREC, typename ACC, bool GATED = false, bool MASKED = false, int NB = 1>
 __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, ACC *acc, int S, int C, int T,
                                               int splits, int kb, int sp, uint8_t *lds,
                                               const uint8_t *__restrict__ gate = nullptr, int bin = 0,
-                                              const uint32_t *__restrict__ keep = nullptr) {
+                                              const uint32_t *__restrict__ keep = nullptr, int half = 0,
+                                              int n_bins = 0, int64_t acc_elems = 0) {
+    static_assert(NB == 1 || (NB == 2 && GATED && !MASKED && PREC != CORR_FP32), "bins per workgroup");
     using V16 = typename std::conditional<PREC == CORR_INT8, v16i, v16f>::type;
-    const int wv = threadIdx.x >> 6, c = kXWaves * kb + wv;
+    constexpr int NCH = kXWaves / NB;                                  // channels of the workgroup
+    constexpr int kRowPitch = NB == 1 ? corr::kRowPitch : 80;          // bytes per signal row: NCH x 16 and a pad of 16
+    constexpr int kBlk = kMaxSignals * kRowPitch;
+    const int wv = threadIdx.x >> 6, ch = wv % NCH, c = kXWaves * kb + half * NCH + ch;
+    if constexpr (NB > 1) bin += wv / NCH;
     const int lane = threadIdx.x & 63, row = lane & 31, lg = lane >> 5;
     const int G = (PREC == CORR_FP32) ? kChunk32 : kChunk8;
     const int steps = T / G / 4 / splits;
@@ -159,13 +169,17 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
     if (steps < 1) return;  // no K-step (the plan's splits always leave one): nothing to add
 
     // staging copy: thread i moves bytes [16 i, 16 i + 16) of each block
-    const int i = threadIdx.x;
-    const bool cp = i < S * 8;
-    const int lds_dst = (i >> 3) * kRowPitch + (i & 7) * 16;
+    // (NB = 2: unit i mod 256 of the workgroup's 4 channels, threads 0..255 in the
+    // blocks 0 and 2 of a K-step, the others in 1 and 3)
+    const int i = threadIdx.x, u = NB == 1 ? i : i & 255;
+    const bool cp = u < S * NCH;
+    const int lds_dst = (u / NCH) * kRowPitch + (u % NCH) * 16 + (NB == 1 ? 0 : (i >> 8) * kBlk);
     // threads beyond the block load its last 16 bytes and discard them, so
     // every thread issues the same loads (the compiler can then count the
     // loads in flight across steps and wait only for the older set)
-    const uint4 *gsrc = reinterpret_cast<const uint4 *>(spec) + (int64_t)kb * S * 8 + (cp ? i : S * 8 - 1);
+    const int unit = cp ? u : S * NCH - 1;
+    const uint4 *gsrc = reinterpret_cast<const uint4 *>(spec) + (int64_t)kb * S * 8 + (unit / NCH) * 8 + half * NCH +
+                        unit % NCH + (NB == 1 ? 0 : (i >> 8) * (int64_t)C * S);
     const int64_t gstride = (int64_t)C * S;  // 16-byte units between chunks g and g+1
     // keep words of this thread's (channel, signal): a K-step's 4 chunks are 32
     // spectra (one word) for INT8 / FP8 and 8 spectra (one byte) for FP32; the
@@ -184,9 +198,11 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
         const int64_t s_ = (int64_t)sp * steps + (st);                \
         const uint4 *g_ = gsrc + 4 * s_ * gstride;                    \
         R##0 = g_[0];                                                 \
-        R##1 = g_[gstride];                                           \
         R##2 = g_[2 * gstride];                                       \
-        R##3 = g_[3 * gstride];                                       \
+        if constexpr (NB == 1) {                                      \
+            R##1 = g_[gstride];                                       \
+            R##3 = g_[3 * gstride];                                   \
+        }                                                             \
         if constexpr (MASKED) {                                       \
             if constexpr (PREC == CORR_FP32)                          \
                 R##k = kw0[(s_ >> 2) * kwstride] >> (8 * (s_ & 3));   \
@@ -205,9 +221,11 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
             R##3 = keep_chunk<PREC>(R##3, R##k >> (3 * SH_));         \
         }                                                             \
         *reinterpret_cast<uint4 *>(l_) = R##0;                        \
-        *reinterpret_cast<uint4 *>(l_ + kBlk) = R##1;                 \
         *reinterpret_cast<uint4 *>(l_ + 2 * kBlk) = R##2;             \
-        *reinterpret_cast<uint4 *>(l_ + 3 * kBlk) = R##3;             \
+        if constexpr (NB == 1) {                                      \
+            *reinterpret_cast<uint4 *>(l_ + kBlk) = R##1;             \
+            *reinterpret_cast<uint4 *>(l_ + 3 * kBlk) = R##3;         \
+        }                                                             \
     }
 
     V16 accR[ntri(NT)], accM[NT * NT];
@@ -218,6 +236,21 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
     bool valid[NT];
 #pragma unroll
     for (int a = 0; a < NT; ++a) valid[a] = (32 * a + row) < S;
+
+    // gates of a K-step's 4 G spectra (GATED)
+    struct GateStep {
+        uint32_t w[PREC == CORR_FP32 ? 2 : 8];
+    };
+    auto gate_step = [&](int st) __attribute__((always_inline)) {
+        GateStep g = {};
+        if constexpr (GATED) {
+            const uint32_t *w = reinterpret_cast<const uint32_t *>(gate) + ((int64_t)sp * steps + st) * G;
+#pragma unroll
+            for (int q = 0; q < (int)(sizeof(g.w) / 4); ++q) g.w[q] = w[q];
+        }
+        return g;
+    };
+    GateStep gates = gate_step(0);
 
     X_GLOAD(0, pa)
     X_LSTORE(0, pa)
@@ -239,31 +272,36 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
         v4i c0[NT], c1[NT];
 #pragma unroll
         for (int a = 0; a < NT; ++a) {
-            const uint8_t *b = lds + (buf * 4 + lg) * kBlk + (32 * a + row) * kRowPitch + wv * 16;
+            const uint8_t *b = lds + (buf * 4 + lg) * kBlk + (32 * a + row) * kRowPitch + ch * 16;
             c0[a] = valid[a] ? *reinterpret_cast<const v4i *>(b) : v4i{0};
             c1[a] = valid[a] ? *reinterpret_cast<const v4i *>(b + 2 * kBlk) : v4i{0};
         }
         // B operands: masked to the gate's spectra when GATED
         v4i b0[NT], b1[NT];
         if constexpr (GATED) {
-            // this lane's chunks are g0 + lg and g0 + 2 + lg, g0 = 4 (sp steps + st)
-            const int64_t g = 4 * ((int64_t)sp * steps + st) + lg;
+            // the K-step's gates, the same in every lane: scalar loads a step ahead and
+            // byte masks on the scalar unit (as vector loads their wait, in order
+            // behind them, drained the spectra's prefetch at every step); then this lane's
+            // chunks are g0 + lg and g0 + 2 + lg
             const uint32_t b4 = (uint32_t)bin * 0x01010101u;
+            const GateStep gs = gates;
+            gates = gate_step(st + 1 < steps ? st + 1 : st);
             if constexpr (PREC == CORR_FP32) {  // 2 spectra per chunk: one mask word per spectrum
-                const uint16_t q0 = *reinterpret_cast<const uint16_t *>(gate + 2 * g);
-                const uint16_t q1 = *reinterpret_cast<const uint16_t *>(gate + 2 * (g + 2));
-                const int m00 = (q0 & 0xFF) == bin ? -1 : 0, m01 = (q0 >> 8) == bin ? -1 : 0;
-                const int m10 = (q1 & 0xFF) == bin ? -1 : 0, m11 = (q1 >> 8) == bin ? -1 : 0;
+                const uint32_t e0 = eq_bytes(gs.w[0], b4), e1 = eq_bytes(gs.w[1], b4);
+                const uint32_t q0 = lg ? e0 >> 16 : e0, q1 = lg ? e1 >> 16 : e1;
+                const int m00 = -(int)(q0 & 1u), m01 = -(int)((q0 >> 8) & 1u);
+                const int m10 = -(int)(q1 & 1u), m11 = -(int)((q1 >> 8) & 1u);
 #pragma unroll
                 for (int a = 0; a < NT; ++a) {
                     b0[a] = v4i{c0[a].x & m00, c0[a].y & m00, c0[a].z & m01, c0[a].w & m01};
                     b1[a] = v4i{c1[a].x & m10, c1[a].y & m10, c1[a].z & m11, c1[a].w & m11};
                 }
             } else {  // 8 spectra per chunk: real bytes 0-7, imaginary bytes 8-15
-                const uint2 q0 = *reinterpret_cast<const uint2 *>(gate + 8 * g);
-                const uint2 q1 = *reinterpret_cast<const uint2 *>(gate + 8 * (g + 2));
-                const int m0l = (int)eq_bytes(q0.x, b4), m0h = (int)eq_bytes(q0.y, b4);
-                const int m1l = (int)eq_bytes(q1.x, b4), m1h = (int)eq_bytes(q1.y, b4);
+                uint32_t e[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) e[q] = eq_bytes(gs.w[q], b4);
+                const int m0l = (int)(lg ? e[2] : e[0]), m0h = (int)(lg ? e[3] : e[1]);
+                const int m1l = (int)(lg ? e[6] : e[4]), m1h = (int)(lg ? e[7] : e[5]);
 #pragma unroll
                 for (int a = 0; a < NT; ++a) {
                     b0[a] = v4i{c0[a].x & m0l, c0[a].y & m0h, c0[a].z & m0l, c0[a].w & m0h};
@@ -368,7 +406,8 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
 #undef X_LSTORE
     // the staging buffers are free now: the epilogue's M-tile exchange reuses them
     auto *mlds = reinterpret_cast<ACC(*)[32][33]>(lds + wv * NT * NT * 32 * 33 * 4);
-    x_epilogue<NT, ACC>(accR, accM, acc + ((int64_t)sp * C + c) * P * 2, S, P, mlds);
+    if constexpr (NB > 1) acc += bin * acc_elems;
+    x_epilogue<NT, ACC>(accR, accM, acc + ((int64_t)sp * C + c) * P * 2, NB == 1 || bin < n_bins ? S : 0, P, mlds);
     __syncthreads();  // the LDS may be reused by the next block of a persistent loop
 }
 
@@ -504,11 +543,15 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
             }
         }
     };
+    // the gates of a step are the same in every lane: scalar loads (a vector load's
+    // wait would drain the chunks in flight)
     auto load_gate = [&](int st) __attribute__((always_inline)) {
         if constexpr (GATED) {
-            const int64_t g = 2 * kSplitChunks * ((int64_t)sp * steps + st) + 8 * lg;
-            const uint2 q = *reinterpret_cast<const uint2 *>(gate + g);
-            const uint32_t b4 = (uint32_t)bin * 0x01010101u, lo = eq_bytes(q.x, b4), hi = eq_bytes(q.y, b4);
+            const uint32_t *w = reinterpret_cast<const uint32_t *>(gate) + 4 * ((int64_t)sp * steps + st);
+            const uint32_t b4 = (uint32_t)bin * 0x01010101u;
+            const uint32_t e0 = eq_bytes(w[0], b4), e1 = eq_bytes(w[1], b4), e2 = eq_bytes(w[2], b4),
+                           e3 = eq_bytes(w[3], b4);
+            const uint32_t lo = lg ? e2 : e0, hi = lg ? e3 : e1;
             m = v4u{__builtin_amdgcn_perm(0u, lo, 0x01010000u), __builtin_amdgcn_perm(0u, lo, 0x03030202u),
                     __builtin_amdgcn_perm(0u, hi, 0x01010000u), __builtin_amdgcn_perm(0u, hi, 0x03030202u)};
         }
@@ -656,29 +699,36 @@ xengine_kernel(const uint8_t *__restrict__ spec, const uint32_t *__restrict__ ke
     }
 }
 
-// Gated correlation: one workgroup per (task, bin), task = (channel block kb,
-// split sp); it sums the spectra of gate bin `bin` into accumulator set
-// `bin` (acc_elems elements apart).  Every bin reads the same spectra, so the
-// bins of one task are given ids 8 apart: workgroups go to the 8 XCDs in
-// turn, so those land on the same XCD, run side by side and share its L2
-// (the later reads hit).  w -> xcd = w mod 8, j = w / 8, bin = j mod n_bins,
-// task = 8 (j / n_bins) + xcd.
-template <int NT, int PREC, typename ACC>
+// Gated correlation: task = (channel block kb, split sp); it sums the spectra of
+// gate bin `bin` into accumulator set `bin` (acc_elems elements apart).  A task
+// has `per` workgroups: one per bin (NB = 1), or, for 8-bit codes, one per channel
+// half and pair of bins (NB = 2), so that the spectra are staged once for two
+// bins instead of once for each: two bins at 64 x 2048 x 8192 int8 take 545 us,
+// 660 us with NB = 1 (and 860 us before the gates came by scalar loads; the
+// spectra's 2.1 GB take 365 us at the card's read rate).  The workgroups of a task read the
+// same lines, so they are given ids 8 apart: workgroups go to the 8 XCDs in turn,
+// so those land on the same XCD, run side by side and share its L2 (the later
+// reads hit).  w -> xcd = w mod 8, j = w / 8, part = j mod per,
+// task = 8 (j / per) + xcd.
+template <int NT, int PREC, typename ACC, int NB>
 __global__ void __launch_bounds__(64 * kXWaves)
 xengine_gated_kernel(const uint8_t *__restrict__ spec, const uint8_t *__restrict__ gate, ACC *acc, int64_t acc_elems,
                      int S, int C, int T, int splits, int n_bins) {
-    __shared__ __attribute__((aligned(16))) uint8_t
-        lds[x_lds_bytes<NT>()];
+    __shared__ __attribute__((aligned(16))) uint8_t lds[x_lds_bytes<NT>()];
+    const int per = NB * ((n_bins + NB - 1) / NB);
     const int w = blockIdx.x, xcd = w & (kXcds - 1), j = w / kXcds;
-    const int bin = j % n_bins, task = kXcds * (j / n_bins) + xcd;
+    const int part = j % per, task = kXcds * (j / per) + xcd;
     const int nkb = C / kXWaves;
     if (task >= nkb * splits) return;  // padding of the last group of 8 tasks
     if constexpr (PREC == CORR_FP32)
-        xengine_block_split<NT, true, false>(spec, acc + bin * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds,
-                                             gate, bin, nullptr);
+        xengine_block_split<NT, true, false>(spec, acc + part * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds,
+                                             gate, part, nullptr);
+    else if constexpr (NB == 1)
+        xengine_block<NT, PREC, ACC, true>(spec, acc + part * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds,
+                                           gate, part);
     else
-        xengine_block<NT, PREC, ACC, true>(spec, acc + bin * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds,
-                                           gate, bin);
+        xengine_block<NT, PREC, ACC, true, false, 2>(spec, acc, S, C, T, splits, task % nkb, task / nkb, lds, gate,
+                                                     part / 2 * 2, nullptr, part % 2, n_bins, acc_elems);
 }
 
 // One launch over the tasks of a batch of correlations of different shapes
@@ -864,21 +914,30 @@ hipError_t launch_xengine(int precision, const void *spec, const uint32_t *keep,
 hipError_t launch_xengine_gated(int precision, const void *spec, const uint8_t *gate, int n_bins, void *acc,
                                 int64_t acc_elems, int S, int C, int T, int splits, hipStream_t st) {
     const int tasks = (C / kXWaves) * splits;
-    const dim3 grid((unsigned)((tasks + kXcds - 1) / kXcds * kXcds * n_bins)), block(64 * kXWaves);
+    // pairs of bins (545 us for two at 64 x 2048 x 8192 int8, 330 us a bin alone): not for
+    // three, whose second pair is half empty (1090 against 990 us)
+    const bool pair = precision != CORR_FP32 && n_bins > 1 && n_bins != 3;
+    const int per = pair ? 2 * ((n_bins + 1) / 2) : n_bins;
+    const dim3 grid((unsigned)((tasks + kXcds - 1) / kXcds * kXcds * per)), block(64 * kXWaves);
     const uint8_t *sp8 = (const uint8_t *)spec;
+    auto go = [&](auto kernel, auto *a) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, sp8, gate, a, acc_elems, S, C, T, splits, n_bins);
+    };
     const bool two = S > 32;
+    int32_t *ai = (int32_t *)acc;
+    float *af = (float *)acc;
     switch (precision) {
     case CORR_INT8:
-        if (two) hipLaunchKernelGGL((xengine_gated_kernel<2, CORR_INT8, int32_t>), grid, block, 0, st, sp8, gate, (int32_t *)acc, acc_elems, S, C, T, splits, n_bins);
-        else hipLaunchKernelGGL((xengine_gated_kernel<1, CORR_INT8, int32_t>), grid, block, 0, st, sp8, gate, (int32_t *)acc, acc_elems, S, C, T, splits, n_bins);
+        if (two) pair ? go(xengine_gated_kernel<2, CORR_INT8, int32_t, 2>, ai) : go(xengine_gated_kernel<2, CORR_INT8, int32_t, 1>, ai);
+        else pair ? go(xengine_gated_kernel<1, CORR_INT8, int32_t, 2>, ai) : go(xengine_gated_kernel<1, CORR_INT8, int32_t, 1>, ai);
         break;
     case CORR_FP8_E4M3:
-        if (two) hipLaunchKernelGGL((xengine_gated_kernel<2, CORR_FP8_E4M3, float>), grid, block, 0, st, sp8, gate, (float *)acc, acc_elems, S, C, T, splits, n_bins);
-        else hipLaunchKernelGGL((xengine_gated_kernel<1, CORR_FP8_E4M3, float>), grid, block, 0, st, sp8, gate, (float *)acc, acc_elems, S, C, T, splits, n_bins);
+        if (two) pair ? go(xengine_gated_kernel<2, CORR_FP8_E4M3, float, 2>, af) : go(xengine_gated_kernel<2, CORR_FP8_E4M3, float, 1>, af);
+        else pair ? go(xengine_gated_kernel<1, CORR_FP8_E4M3, float, 2>, af) : go(xengine_gated_kernel<1, CORR_FP8_E4M3, float, 1>, af);
         break;
     case CORR_FP32:
-        if (two) hipLaunchKernelGGL((xengine_gated_kernel<2, CORR_FP32, float>), grid, block, 0, st, sp8, gate, (float *)acc, acc_elems, S, C, T, splits, n_bins);
-        else hipLaunchKernelGGL((xengine_gated_kernel<1, CORR_FP32, float>), grid, block, 0, st, sp8, gate, (float *)acc, acc_elems, S, C, T, splits, n_bins);
+        if (two) go(xengine_gated_kernel<2, CORR_FP32, float, 1>, af);
+        else go(xengine_gated_kernel<1, CORR_FP32, float, 1>, af);
         break;
     default:
         return hipErrorInvalidValue;
