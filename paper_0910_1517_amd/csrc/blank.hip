@@ -10,24 +10,28 @@
 // replacements of different antennas are independent.  A block with MAD = 0
 // has no scale estimate and passes unchanged.
 //
-// One workgroup per (block, signal).  The block (up to 64 KiB) is loaded once
-// into registers and never re-read.  int8 has 256 values, so the median and
-// the MAD are exact order statistics of a 256-bin histogram built with LDS
-// atomics.  The counters are 32 bits wide, one bin to a word, in 16 copies
-// (thread t adds to copy t mod 16); the whole histogram is 16 KiB.  After the
-// block-wide inclusive prefix sum P of the merged histogram:
-//   k-th smallest sample           = #{u : P[u] < k} - 128,
-//   #{samples with |2x - 2x~| <= D} = P[hi(D)] - P[lo(D) - 1], a range query,
-//   k-th smallest |2x - 2x~|       = #{D : count(D) < k},
-// each one block-wide count, with no sort.  The threshold test
-// |x - x~| > M MAD / 0.6745 is one FP64 expression per block, turned into
-// the integer range [lo, hi] of values kept.  The number blanked comes from P
-// too.  Eq. 4 is applied to four samples per instruction (byte-wise
-// arithmetic in 32-bit words).  The blanked positions of a block are queued in
-// the histogram's LDS, and all threads then compute their replacements from
-// the table in FP64 and store them as single bytes.  Out of place, the block
-// is copied right after it is loaded and the replacements patch the copy; in
-// place, only the blanked bytes are written.
+// A block (up to 64 KiB) is loaded once into registers, 32 G samples a lane,
+// by one wave up to 8192 samples and by two, four or eight above, and never
+// re-read.  Its statistics are exact order statistics taken bit by bit: each
+// group of 32 samples of a lane is transposed into 8 words, one per bit (word
+// p holds bit p of the 32 samples), after which one instruction handles 32
+// samples.  The k-th smallest value is found from its top bit down: of the
+// candidates, count those with the bit clear; if k of them or more, keep
+// these, else keep the others and take k less.  |x - x~| is a subtraction in
+// the same form (the median is uniform, so its bits are constants), the
+// comparison of Eq. 4 another.  What it costs: about 50 instructions of
+// transposing and 90 of selection per 32 samples, and one sum over the wave
+// per bit.  A histogram, the other way to the same numbers, needs one LDS atomic
+// per sample: 64 x 8388613 four-bit samples in blocks of 4096 took 424 us that
+// way, now 200 us (0.54 GB read; 91 us at the card's read rate; the vector ALUs
+// are busy 92% of it), 64 x 2^24 eight-bit samples in blocks of 4096 582 us, now
+// 297, in blocks of 16384 297 and 285.
+// The threshold test |x - x~| > M MAD / 0.6745 is one FP64 expression per
+// block, turned into the integer range [lo, hi] of values kept.  The blanked
+// positions of a block are queued in LDS, and all lanes then compute their
+// replacements from the table in FP64 and store them as single bytes.  Out of
+// place, the block is copied right after it is loaded and the replacements patch
+// the copy; in place, only the blanked bytes are written.
 //
 // Noise table: entry j of signal s is the Irwin-Hall sum of twelve 16-bit
 // uniforms (U + 1/2) / 65536, minus 6.  The uniforms are the 16-bit halves
@@ -47,12 +51,9 @@
 
 namespace {
 
-constexpr int kBlankThreads = 256;
-constexpr int kBlankWaves = kBlankThreads / 64;
-constexpr int kHistCopies = 16;                     // thread t adds to copy t mod 16
-constexpr int kQueueCap = 256 * kHistCopies * 2;    // 16-bit positions in the histogram's memory
+constexpr int kBlankQueue = 2048;                 // 16-bit positions a wave's LDS queue holds
 constexpr int kBlankMaxSignals = 65535;           // grid y
-constexpr int kBlankMaxBlock = 65536;             // 16 chunks of 16 B per thread
+constexpr int kBlankMaxBlock = 65536;             // eight waves of 8192 samples
 constexpr int64_t kBlankMaxTable = 1ll << 31;
 
 // ---------------------------------------------------------------- Philox
@@ -89,26 +90,25 @@ __global__ __launch_bounds__(256) void noise_table_kernel(uint32_t k0, uint32_t 
 }
 
 // ---------------------------------------------------------------- blanker
-// Sum of v over the workgroup (every thread gets it).
-__device__ inline uint32_t block_sum(uint32_t v, uint32_t *red) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    __syncthreads();  // red may still be read from a previous use
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    uint32_t t = 0;
-#pragma unroll
-    for (int w = 0; w < kBlankWaves; ++w) t += red[w];
-    return t;
+// Inclusive prefix sum of v over the wave's lanes: row shifts, then the totals
+// of the rows before.
+__device__ inline uint32_t wave_prefix(uint32_t v) {
+    int x = (int)v;
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, true);  // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, true);  // row_bcast:31 into rows 2 and 3
+    return (uint32_t)x;
 }
 
-// Number of samples with |2x - med2| <= D, from the inclusive prefix sums
-// cum[u] over biased values u = x + 128.
-__device__ inline int dev_count(const uint32_t *cum, int med2, int D) {
-    const int hi = min(((med2 + D) >> 1) + 128, 255);     // floor((med2 + D) / 2)
-    const int lo = max(-((D - med2) >> 1) + 128, 0);      // ceil((med2 - D) / 2)
-    if (hi < lo) return 0;
-    return (int)cum[hi] - (lo ? (int)cum[lo - 1] : 0);
+// v / 0.6745, correctly rounded: a first quotient from the rounded reciprocal,
+// corrected once by its exact remainder (Markstein).  v is 0 or at least 2^-151.
+__device__ inline double over_6745(double v) {
+    constexpr double c = 0.6745, y = 1.0 / c;
+    const double q = v * y;
+    return fma(fma(-q, c, v), y, q);
 }
 
 // Replacement value of a blanked sample: rint(x~ + sigma z), clamped, all in
@@ -120,283 +120,262 @@ __device__ inline uint32_t replacement(double half_med2, double sigma, float z) 
     return (uint32_t)(int32_t)r & 0xFFu;
 }
 
-// Eq. 4 for four samples at once: bit 7 of byte i of the result is set when
-// byte i of w (a signed sample) lies outside [lo, hi].  d = (x - lo) mod 256
-// per byte, without borrows between bytes (lo_lo7 = low seven bits of lo in
-// every byte, lo_hi = bit 7 of ~lo in every byte); the sample is outside when
-// d > span = hi - lo.  WIDE (span >= 128): d > span <=> d >= 128 and its low
-// seven bits exceed span - 128; otherwise d >= 128 or its low seven bits
-// exceed span.
-template <bool WIDE>
-__device__ inline uint32_t outside4(uint32_t w, uint32_t lo_lo7, uint32_t lo_hi, uint32_t c7) {
-    const uint32_t d = ((w | 0x80808080u) - lo_lo7) ^ (w & 0x80808080u) ^ lo_hi;
-    const uint32_t gt = (d & 0x7F7F7F7Fu) + c7;  // bit 7 set <=> low seven bits > (span mod 128)
-    return (WIDE ? (d & gt) : (d | gt)) & 0x80808080u;
-}
-
-// Replace the flagged bytes of one chunk (f[d]: bit 7 of byte k set = byte
-// 4 d + k flagged), one at a time.
-__device__ inline void replace_chunk(uint32_t w4[4], const uint32_t f[4], const float *trow, int64_t p0,
-                                     int64_t Lmask, double half_med2, double sigma) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        uint32_t m = f[d];
-        while (m) {
-            const int k = __builtin_ctz(m) >> 3;
-            m &= m - 1;
-            const uint32_t r = replacement(half_med2, sigma, trow[(p0 + 4 * d + k) & Lmask]);
-            w4[d] = (w4[d] & ~(0xFFu << (8 * k))) | (r << (8 * k));
-        }
-    }
-}
-
-struct BlankShared {
-    // 256 raw byte values x 16 copies of a 32-bit counter: bin r of copy c at
-    // word 16 r + c.  After the merge the same memory holds the queue of
-    // blanked positions.
-    uint32_t hist[256 * kHistCopies];
-    uint32_t cum[256];
-    uint32_t red[kBlankWaves];
-};
-
-// One block of `len` samples (len < B only for a row's last block: TAIL).
-template <int J, bool TAIL>
-__device__ inline void blank_block(BlankShared &sh, const uint4 (&v)[J], int len, int8_t *orow, double M,
-                                   const float *trow, int64_t Lmask, int64_t p_blk, int32_t *count_out,
-                                   int32_t *stat_out, bool in_place) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-
-    // histogram (the counters were zeroed before the first barrier): raw byte
-    // r of the sample, copy tid mod 16
-    uint32_t *hl = sh.hist + (tid & (kHistCopies - 1));
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int c = tid + kBlankThreads * j;
-        const int nv = len - c * 16;
-        if (nv <= 0) continue;
-        const uint32_t w4[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            if (TAIL && k >= nv) break;
-            __hip_atomic_fetch_add(hl + ((w4[k >> 2] >> (8 * (k & 3))) & 0xFFu) * kHistCopies, 1u,
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-    }
-    __syncthreads();
-
-    // merge: thread t owns bin u = t (raw byte u ^ 0x80) and sums its copies
-    // (the start is rotated so that a wave's lanes spread over the banks),
-    // then the block-wide inclusive prefix sum over bins
-    const int u = tid;
-    uint32_t h = 0;
-    {
-        const uint4 *row = reinterpret_cast<const uint4 *>(sh.hist) + (u ^ 0x80) * (kHistCopies / 4);
-#pragma unroll
-        for (int q = 0; q < kHistCopies / 4; ++q) {
-            const uint4 r = row[(q + u) & (kHistCopies / 4 - 1)];
-            h += r.x + r.y + r.z + r.w;
-        }
-    }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = __shfl_up(h, off, 64);
-        if (lane >= off) h += t;
-    }
-    if (lane == 63) sh.red[wave] = h;
-    __syncthreads();
-    for (int w = 0; w < wave; ++w) h += sh.red[w];
-    sh.cum[u] = h;  // cum[u] = #{samples with x + 128 <= u}
-
-    // median (Eq. 3): the k1-th and k2-th smallest samples (equal for odd
-    // len) are #{u : cum[u] < k} - 128; med2 = their sum = 2 x~
-    const uint32_t k1 = (uint32_t)(len + 1) >> 1, k2 = (uint32_t)(len >> 1) + 1;
-    const uint32_t cm = block_sum((h < k1 ? 1u : 0u) | (h < k2 ? 0x10000u : 0u), sh.red);
-    const int med2 = (int)(cm & 0xFFFFu) + (int)(cm >> 16) - 256;
-
-    // MAD (Eq. 3): the k1-th and k2-th smallest of d = |2x - med2| in
-    // [0, 510] are #{D : count(d <= D) < k}; thread t tests D = t and t + 256
-    const int cA = dev_count(sh.cum, med2, tid), cB = dev_count(sh.cum, med2, tid + 256);
-    const uint32_t pd = ((uint32_t)(cA < (int)k1) + (uint32_t)(cB < (int)k1)) |
-                        (((uint32_t)(cA < (int)k2) + (uint32_t)(cB < (int)k2)) << 16);
-    const uint32_t cd = block_sum(pd, sh.red);
-    const int mad4 = (int)(cd & 0xFFFFu) + (int)(cd >> 16);
-
-    // Eq. 4 as an integer range: keep lo <= x <= hi; the number blanked
-    // comes from the prefix sums
-    int lo = -128, hi = 127;
-    if (mad4 > 0) {
-        const double mad = (double)mad4 * 0.25;
-        const double thr2 = 2.0 * ((M * mad) / 0.6745);  // |2x - med2| > thr2 blanks
-        const int dmax = thr2 >= 511.0 ? 511 : (int)floor(thr2);
-        hi = min((med2 + dmax) >> 1, 127);
-        lo = max(-((dmax - med2) >> 1), -128);
-    }
-    const int below = lo > -128 ? (int)sh.cum[lo + 127] : 0;
-    const int above = hi < 127 ? len - (int)sh.cum[hi + 128] : 0;
-    const int n_out = below + above;
-    if (tid == 0) {
-        if (count_out) *count_out = n_out;
-        if (stat_out) {
-            stat_out[0] = med2;
-            stat_out[1] = mad4;
-        }
-    }
-    if (n_out == 0) return;  // nothing to blank (uniform)
-
-    // flag four samples per instruction
-    const uint32_t span = (uint32_t)(hi - lo);
-    const uint32_t lo_rep = (uint32_t)(lo & 0xFF) * 0x01010101u;
-    const uint32_t lo_lo7 = lo_rep & 0x7F7F7F7Fu, lo_hi = ~lo_rep & 0x80808080u;
-    const uint32_t c7 = (127u - (span & 127u)) * 0x01010101u;
-    const bool wide = span >= 128;
-    // flags of chunk j, word d (bit 7 of each outlier byte); kept in
-    // registers for up to four chunks per thread, recomputed beyond
-    auto flags = [&](int j, int d) -> uint32_t {
-        const int nv = len - (tid + kBlankThreads * j) * 16;
-        const uint32_t w = d == 0 ? v[j].x : d == 1 ? v[j].y : d == 2 ? v[j].z : v[j].w;
-        uint32_t fd = wide ? outside4<true>(w, lo_lo7, lo_hi, c7) : outside4<false>(w, lo_lo7, lo_hi, c7);
-        if (TAIL) {  // bytes past the row's end are never flagged
-            const int keep = min(max(nv - 4 * d, 0), 4);
-            fd &= keep >= 4 ? 0xFFFFFFFFu : ((1u << (8 * keep)) - 1u);
-        } else if (nv <= 0) {
-            fd = 0u;
-        }
-        return fd;
+// Bits of 32 samples, one word per sample bit: word p, bit 8 b + r = bit p of
+// byte b of w[r] (an 8 x 8 bit transpose in each byte lane).
+__device__ inline void bit_planes(uint32_t (&w)[8]) {
+    auto swap = [&](int i, int j, int sh, uint32_t m) {  // exchange the sh-bit fields of rows i < j
+        const uint32_t a = w[i], b = w[j];
+        w[i] = (a & m) | ((b << sh) & ~m);
+        w[j] = ((a >> sh) & m) | (b & ~m);
     };
-    constexpr bool kKeep = J <= 4;
-    uint32_t f[kKeep ? J : 1][4];
-    uint32_t mine = 0;
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
+    for (int i = 0; i < 4; ++i) swap(i, i + 4, 4, 0x0F0F0F0Fu);
 #pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const uint32_t fd = flags(j, d);
-            if (kKeep) f[kKeep ? j : 0][d] = fd;
-            mine += (uint32_t)__builtin_popcount(fd);
-        }
-    }
-
-    // block-wide exclusive scan of the per-thread counts
-    uint32_t pre = mine;
+    for (int i = 0; i < 8; ++i)
+        if (!(i & 2)) swap(i, i + 2, 2, 0x33333333u);
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = __shfl_up(pre, off, 64);
-        if (lane >= off) pre += t;
-    }
-    __syncthreads();  // red is reused; the histogram words are free after the merge
-    if (lane == 63) sh.red[wave] = pre;
-    __syncthreads();
-    uint32_t base = pre - mine;
-    for (int w = 0; w < wave; ++w) base += sh.red[w];
-    uint32_t total = 0;
-#pragma unroll
-    for (int w = 0; w < kBlankWaves; ++w) total += sh.red[w];  // equals n_out
-
-    const double half_med2 = 0.5 * (double)med2;
-    const double sigma = ((double)mad4 * 0.25) / 0.6745;
-    if (total > (uint32_t)kQueueCap) {
-        // more outliers than the queue holds (possible only for blocks longer
-        // than 2 kQueueCap samples, since fewer than half the samples of a
-        // block lie beyond M MAD / 0.6745 >= MAD for the usual M): each thread
-        // patches its own chunks
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int c = tid + kBlankThreads * j;
-            const int nv = len - c * 16;
-            uint32_t fj[4];
-#pragma unroll
-            for (int d = 0; d < 4; ++d) fj[d] = kKeep ? f[kKeep ? j : 0][d] : flags(j, d);
-            if ((fj[0] | fj[1] | fj[2] | fj[3]) == 0u) continue;
-            uint32_t w4[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-            replace_chunk(w4, fj, trow, p_blk + (int64_t)c * 16, Lmask, half_med2, sigma);
-            if (!TAIL || nv >= 16) {
-                *reinterpret_cast<uint4 *>(orow + c * 16) = make_uint4(w4[0], w4[1], w4[2], w4[3]);
-            } else {
-                for (int k = 0; k < nv; ++k) orow[c * 16 + k] = (int8_t)(w4[k >> 2] >> (8 * (k & 3)));
-            }
-        }
-        return;
-    }
-
-    // queue the blanked positions, then replace them with all threads busy
-    uint16_t *queue = reinterpret_cast<uint16_t *>(sh.hist);
-#pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int c = tid + kBlankThreads * j;
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            uint32_t m = kKeep ? f[kKeep ? j : 0][d] : flags(j, d);
-            while (m) {
-                const int bit = __builtin_ctz(m);
-                m &= m - 1;
-                queue[base++] = (uint16_t)(c * 16 + 4 * d + (bit >> 3));
-            }
-        }
-    }
-    __syncthreads();
-    for (int e = tid; e < (int)total; e += kBlankThreads) {
-        const int pos = queue[e];
-        orow[pos] = (int8_t)replacement(half_med2, sigma, trow[(p_blk + pos) & Lmask]);
-    }
+    for (int i = 0; i < 8; i += 2) swap(i, i + 1, 1, 0x55555555u);
 }
 
-template <int J>
-__global__ __launch_bounds__(kBlankThreads) void blank_kernel(const int8_t *__restrict__ x, int8_t *out,
-                                                              int64_t row_stride, int64_t n, int B, double M,
-                                                              const float *__restrict__ table, int64_t L,
-                                                              int64_t sample0, int32_t *counts, int32_t *stats,
-                                                              int in_place) {
-    __shared__ __attribute__((aligned(16))) BlankShared sh;
-    const int tid = threadIdx.x;
+// NW waves hold one block, G groups of 32 samples a lane (a workgroup of four
+// waves has four blocks when NW = 1): group g, chunk h of lane l is chunk
+// l + 64 NW (2 g + h) of the block.  A lane's words past the block's end, whole
+// or in part, are left out by the groups' valid masks.  COPY: how the block gets
+// to the output of a call out of place -- early, as it is loaded, or late, just
+// before the replacements patch it, which finds the lines still in L2 (64 x 2^24
+// samples in blocks of 4096: 522 us early, 395 late; in place 297) where the
+// registers hold the samples meanwhile.
+constexpr int kInPlace = 0, kCopyEarly = 1, kCopyLate = 2;
+template <int G, int NW, int COPY>
+__global__ __launch_bounds__(NW == 1 ? 256 : 64 * NW) void blank_kernel(
+    const int8_t *__restrict__ x, int8_t *out, int64_t row_stride, int64_t n, int B, double M,
+    const float *__restrict__ table, int64_t L, int64_t sample0, int32_t *counts, int32_t *stats) {
+    constexpr int TB = 64 * NW;               // threads of a block
+    constexpr int WPG = NW == 1 ? 4 : NW;     // waves of the workgroup
+    __shared__ uint16_t queue_lds[WPG * kBlankQueue];
+    __shared__ uint32_t red[2][NW];
+    const int t = NW == 1 ? threadIdx.x & 63 : threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t nblk = (n + B - 1) / B, blk = NW == 1 ? (int64_t)blockIdx.x * 4 + wave : blockIdx.x;
+    if (blk >= nblk) return;  // a whole wave; NW = 1 has no barrier
     const int s = blockIdx.y;
-    const int64_t i0 = (int64_t)blockIdx.x * B;
+    const int64_t i0 = blk * B;
     const int len = (int)min((int64_t)B, n - i0);
     const int8_t *xr = x + (int64_t)s * row_stride + i0;
     int8_t *orow = out + (int64_t)s * row_stride + i0;
 
-    // the block's samples, once, into registers; out of place the copy goes
-    // out at once (blanked samples are patched at the end)
-    uint4 v[J];
+    uint32_t u[G][8], valid[G];
 #pragma unroll
-    for (int j = 0; j < J; ++j) {
-        const int c = tid + kBlankThreads * j;
-        v[j] = (c * 16 < len) ? *reinterpret_cast<const uint4 *>(xr + c * 16) : make_uint4(0, 0, 0, 0);
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c = t + TB * (2 * g + h);
+            const uint4 v = c * 16 < len ? *reinterpret_cast<const uint4 *>(xr + c * 16) : make_uint4(0, 0, 0, 0);
+            u[g][4 * h] = v.x;
+            u[g][4 * h + 1] = v.y;
+            u[g][4 * h + 2] = v.z;
+            u[g][4 * h + 3] = v.w;
+        }
+    auto copy = [&](const uint32_t (&v)[G][8]) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int c = t + TB * (2 * g + h), nv = len - c * 16;
+                const uint32_t *w = &v[g][4 * h];
+                if (nv >= 16) {
+                    *reinterpret_cast<uint4 *>(orow + c * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+                } else if (nv > 0) {
+#pragma unroll
+                    for (int k = 0; k < 16; ++k)
+                        if (k < nv) orow[c * 16 + k] = (int8_t)(w[k >> 2] >> (8 * (k & 3)));
+                }
+            }
+    };
+    if constexpr (COPY == kCopyEarly) copy(u);
+    uint32_t raw[COPY == kCopyLate ? G : 1][8];
+    if constexpr (COPY == kCopyLate) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int q = 0; q < 8; ++q) raw[g][q] = u[g][q];
     }
 #pragma unroll
-    for (int q = 0; q < 256 * kHistCopies / 4 / kBlankThreads; ++q)
-        reinterpret_cast<uint4 *>(sh.hist)[tid + kBlankThreads * q] = make_uint4(0, 0, 0, 0);
-    if (!in_place) {
+    for (int g = 0; g < G; ++g) {
+        bit_planes(u[g]);
+        u[g][7] = ~u[g][7];  // two's complement -> x + 128
+        uint32_t m = 0;
 #pragma unroll
-        for (int j = 0; j < J; ++j) {
-            const int c = tid + kBlankThreads * j;
-            const int nv = len - c * 16;
+        for (int h = 0; h < 2; ++h) {
+            const int nv = len - (t + TB * (2 * g + h)) * 16;  // samples of the chunk
             if (nv >= 16) {
-                *reinterpret_cast<uint4 *>(orow + c * 16) = v[j];
-            } else if (nv > 0) {
-                const uint32_t w4[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
-                for (int k = 0; k < nv; ++k) orow[c * 16 + k] = (int8_t)(w4[k >> 2] >> (8 * (k & 3)));
+                m |= 0x0F0F0F0Fu << (4 * h);
+            } else if (nv > 0) {  // sample 4 d + b of the chunk: bit 8 b + 4 h + d
+#pragma unroll
+                for (int k = 0; k < 16; ++k)
+                    if (k < nv) m |= 1u << (8 * (k & 3) + 4 * h + (k >> 2));
             }
         }
+        valid[g] = m;
     }
-    __syncthreads();
 
-    const int64_t b = (int64_t)s * gridDim.x + blockIdx.x;
-    int32_t *cnt = counts ? counts + b : nullptr;
-    int32_t *st = stats ? stats + 2 * b : nullptr;
+    int parity = 0;
+    auto block_total = [&](uint32_t v) -> uint32_t {  // of the waves' totals v
+        if constexpr (NW > 1) {
+            if (t % 64 == 0) red[parity][wave] = v;
+            __syncthreads();  // the other half of red may still be read by a wave behind
+            v = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) v += red[parity][w];
+            v = __builtin_amdgcn_readfirstlane(v);
+            parity ^= 1;
+        }
+        return v;
+    };
+    auto wave_total = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)wave_prefix(v), 63); };
+    // k-th smallest (k >= 1) of the valid values in planes p, and the (k + 1)-th if
+    // there is one
+    auto select = [&](const uint32_t (&p)[G][8], uint32_t k, uint32_t &rest) -> int {
+        uint32_t cand[G], ceq = (uint32_t)len;
+        int value = 0;
+#pragma unroll
+        for (int g = 0; g < G; ++g) cand[g] = valid[g];
+#pragma unroll
+        for (int b = 7; b >= 0; --b) {
+            uint32_t c = 0;
+#pragma unroll
+            for (int g = 0; g < G; ++g) c += __builtin_popcount(cand[g] & ~p[g][b]);
+            c = block_total(wave_total(c));
+            const bool low = k <= c;
+            const uint32_t flip = low ? ~0u : 0u;
+            value |= low ? 0 : 1 << b;
+            k -= low ? 0 : c;
+            ceq = low ? c : ceq - c;
+#pragma unroll
+            for (int g = 0; g < G; ++g) cand[g] &= p[g][b] ^ flip;
+        }
+        rest = ceq - k;  // values equal to it that rank after it
+        return value;
+    };
+    auto select2 = [&](const uint32_t (&p)[G][8], uint32_t k1, uint32_t k2) -> int {  // sum of the two
+        uint32_t rest, unused;
+        const int v1 = select(p, k1, rest);
+        return v1 + (k2 == k1 || rest > 0 ? v1 : select(p, k2, unused));
+    };
+
+    // median (Eq. 3): half the sum of the k1-th and k2-th smallest (equal for odd
+    // len); med2 = 2 x~, medu = 2 (x~ + 128)
+    const uint32_t k1 = (uint32_t)(len + 1) >> 1, k2 = (uint32_t)(len >> 1) + 1;
+    const int medu = select2(u, k1, k2), med2 = medu - 256;
+
+    // MAD (Eq. 3): with m = ceil(medu / 2) and D = u - m, |2 x - med2| is 2 |D| for
+    // an even medu; for an odd one it is 2 D + 1 where D >= 0 and 2 (-D - 1) + 1
+    // where D < 0.  e = |D|, or D with its bits inverted where negative: D xor its
+    // sign, plus the sign when medu is even.
+    const int m = (medu + 1) >> 1;
+    const uint32_t even = (medu & 1) ? 0u : ~0u;
+    // (e takes u's place: Eq. 4 is tested on it)
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        uint32_t borrow = 0;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint32_t mb = ((m >> b) & 1) ? ~0u : 0u, a = u[g][b], d = a ^ mb;
+            u[g][b] = d ^ borrow;
+            borrow = (~a & mb) | (~d & borrow);
+        }
+        uint32_t carry = borrow & even;
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const uint32_t d = u[g][b] ^ borrow;
+            u[g][b] = d ^ carry;
+            carry &= d;
+        }
+    }
+    const int mad4 = 2 * select2(u, k1, k2) + (even ? 0 : 2);
+
+    // Eq. 4, |2x - med2| > 2 M MAD / 0.6745, as e > most: e of 2 e or 2 e + 1
+    int most = 255;
+    if (mad4 > 0) {
+        const double mad = (double)mad4 * 0.25;
+        const double thr2 = 2.0 * over_6745(M * mad);
+        const int dmax = thr2 >= 511.0 ? 511 : (int)floor(thr2);
+        most = even ? dmax >> 1 : (dmax - 1) >> 1;
+    }
+    uint32_t mine = 0, bad[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) bad[g] = 0;
+    if (most < 255) {
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            uint32_t gt = 0;
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const uint32_t hb = ((most >> b) & 1) ? ~0u : 0u, a = u[g][b];
+                gt = (a & ~hb) | (~(a ^ hb) & gt);
+            }
+            bad[g] = (most < 0 ? ~0u : gt) & valid[g];
+            mine += (uint32_t)__builtin_popcount(bad[g]);
+        }
+    }
+    const uint32_t pre = wave_prefix(mine);
+    const int total = __builtin_amdgcn_readlane((int)pre, 63);  // of this wave
+    const int n_out = (int)block_total((uint32_t)total);
+    if (t == 0) {
+        const int64_t o = (int64_t)s * nblk + blk;
+        if (counts) counts[o] = n_out;
+        if (stats) {
+            stats[2 * o] = med2;
+            stats[2 * o + 1] = mad4;
+        }
+    }
+    if constexpr (COPY == kCopyLate) copy(raw);
+    if (n_out == 0) return;  // nothing to blank (uniform over the block)
+
     const float *trow = table + (int64_t)s * L;
-    if (len == B)
-        blank_block<J, false>(sh, v, len, orow, M, trow, L - 1, sample0 + i0, cnt, st, in_place != 0);
-    else
-        blank_block<J, true>(sh, v, len, orow, M, trow, L - 1, sample0 + i0, cnt, st, in_place != 0);
+    const int64_t Lmask = L - 1, p_blk = sample0 + i0;
+    const double half_med2 = 0.5 * (double)med2;
+    const double sigma = over_6745((double)mad4 * 0.25);
+    // bit q of group g of lane l of this wave: chunk, word and byte of the block
+    const int l0 = NW == 1 ? 0 : wave * 64;
+    auto blank = [&](int l, int g, int q) {
+        const int pos = (l0 + l + TB * (2 * g + ((q >> 2) & 1))) * 16 + 4 * (q & 3) + (q >> 3);
+        orow[pos] = (int8_t)replacement(half_med2, sigma, trow[(p_blk + pos) & Lmask]);
+    };
+    if constexpr (NW > 1) __syncthreads();  // out of place: every wave's copy is on its way
+    const int lane = threadIdx.x & 63;
+    if (total > kBlankQueue) {  // more outliers than the queue holds (small M): each lane its own
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+            for (uint32_t w = bad[g]; w; w &= w - 1) blank(lane, g, __builtin_ctz(w));
+        return;
+    }
+    // each wave queues its blanked samples (lane, group, bit), then replaces them
+    // with all its lanes
+    static_assert(G <= 8, "14 bits an entry");
+    uint16_t *queue = queue_lds + wave * kBlankQueue;
+    uint16_t *next = queue + (pre - mine);
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+        for (uint32_t w = bad[g]; w; w &= w - 1) *next++ = (uint16_t)(lane << 8 | g << 5 | __builtin_ctz(w));
+    // the wave's own LDS order suffices
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    for (int i = lane; i < total; i += 64) {
+        const int e = queue[i];
+        blank(e >> 8, (e >> 5) & 7, e & 31);
+    }
 }
 
-template <int J>
-hipError_t launch_blank_j(const int8_t *x, int8_t *out, int64_t row_stride, int S, int64_t n, int B, double M,
-                          const float *table, int64_t L, int64_t sample0, int32_t *counts, int32_t *stats,
-                          hipStream_t st) {
-    const dim3 grid((unsigned)((n + B - 1) / B), (unsigned)S);
-    hipLaunchKernelGGL(blank_kernel<J>, grid, dim3(kBlankThreads), 0, st, x, out, row_stride, n, B, M, table, L,
-                       sample0, counts, stats, (int)(out == x));
+template <int G, int NW, int COPY>
+hipError_t launch_blank(const int8_t *x, int8_t *out, int64_t row_stride, int S, int64_t n, int B, double M,
+                        const float *table, int64_t L, int64_t sample0, int32_t *counts, int32_t *stats,
+                        hipStream_t st) {
+    const int64_t nblk = (n + B - 1) / B;
+    const dim3 grid((unsigned)(NW == 1 ? (nblk + 3) / 4 : nblk), (unsigned)S);
+    hipLaunchKernelGGL((blank_kernel<G, NW, COPY>), grid, dim3(NW == 1 ? 256 : 64 * NW), 0, st, x, out, row_stride, n,
+                       B, M, table, L, sample0, counts, stats);
     return hipGetLastError();
 }
 
@@ -457,24 +436,25 @@ corr_status corr_blank_voltages(const int8_t *d_x, int64_t row_stride, int32_t S
     const int64_t nblk = (n + block - 1) / block;
     if (nblk > 0x7FFFFFFF) return blank_fail(CORR_ERR_INVALID, "more than 2^31 - 1 blocks per row");
     if (n == 0) return CORR_OK;
-    const int J = (block + 16 * kBlankThreads - 1) / (16 * kBlankThreads);
     hipStream_t st = (hipStream_t)stream;
+    auto go = [&](auto launch) {
+        return launch(d_x, d_out, row_stride, S, n, block, (double)M, d_table, table_len, sample0, d_counts, d_stats, st);
+    };
+    // 32 G samples a lane and 64 NW lanes: one wave as far as four waves of it fit the
+    // registers of a SIMD, above that groups of waves, whose sums meet in LDS.  us in
+    // place at 64 x 2^24 samples, blocks of 16384: <8, 1> 444, <4, 2> 272; of 12288: <6, 1>
+    // 295, <4, 2> 420; of 20000: <6, 2> 324, <4, 4> 432; out of place of 65536 early 538,
+    // late 913.
+    const bool in_place = d_out == d_x;
     hipError_t e;
-    if (J <= 1)
-        e = launch_blank_j<1>(d_x, d_out, row_stride, S, n, block, (double)M, d_table, table_len, sample0, d_counts,
-                              d_stats, st);
-    else if (J <= 2)
-        e = launch_blank_j<2>(d_x, d_out, row_stride, S, n, block, (double)M, d_table, table_len, sample0, d_counts,
-                              d_stats, st);
-    else if (J <= 4)
-        e = launch_blank_j<4>(d_x, d_out, row_stride, S, n, block, (double)M, d_table, table_len, sample0, d_counts,
-                              d_stats, st);
-    else if (J <= 8)
-        e = launch_blank_j<8>(d_x, d_out, row_stride, S, n, block, (double)M, d_table, table_len, sample0, d_counts,
-                              d_stats, st);
-    else
-        e = launch_blank_j<16>(d_x, d_out, row_stride, S, n, block, (double)M, d_table, table_len, sample0, d_counts,
-                               d_stats, st);
+    if (block <= 2048) e = in_place ? go(launch_blank<1, 1, kInPlace>) : go(launch_blank<1, 1, kCopyLate>);
+    else if (block <= 4096) e = in_place ? go(launch_blank<2, 1, kInPlace>) : go(launch_blank<2, 1, kCopyLate>);
+    else if (block <= 8192) e = in_place ? go(launch_blank<4, 1, kInPlace>) : go(launch_blank<4, 1, kCopyLate>);
+    else if (block <= 12288 && in_place) e = go(launch_blank<6, 1, kInPlace>);
+    else if (block <= 16384) e = in_place ? go(launch_blank<4, 2, kInPlace>) : go(launch_blank<4, 2, kCopyLate>);
+    else if (block <= 24576 && in_place) e = go(launch_blank<6, 2, kInPlace>);
+    else if (block <= 32768) e = in_place ? go(launch_blank<4, 4, kInPlace>) : go(launch_blank<4, 4, kCopyLate>);
+    else e = in_place ? go(launch_blank<4, 8, kInPlace>) : go(launch_blank<4, 8, kCopyEarly>);
     return e == hipSuccess ? CORR_OK : blank_fail(CORR_ERR_DEVICE, "blanker launch: %s", hipGetErrorString(e));
 }
 
