@@ -333,7 +333,8 @@ fengine_kernel(FLaunch a) {
     const double c_bb = a.nu_bb * (double)g.frac / a.fs;  // baseband term of the phase, cycles
 
     // the spectra's phases, once per workgroup and not by every thread (FP64
-    // reduction, FP32 sincos: ROT_NOTE)
+    // reduction, FP32 sincos: about 50 of 590 vector instructions a spectrum and
+    // wave; int8 1135 -> 1115 us at 64 x 512 x 16384, 1517 -> 1486 us at 64 x 4096 x 2048)
     if constexpr (BM != 3 && !PL) {
         if (threadIdx.x < 16 * FPAR) {
             const int us = threadIdx.x >> 4, rs = threadIdx.x & 15;
