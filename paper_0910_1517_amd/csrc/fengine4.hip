@@ -80,10 +80,12 @@ struct F4Cfg {
     static constexpr int NP8 = LOGN1 / 3;
     static constexpr int RLAST = 1 << (LOGN1 % 3);
     static constexpr int NPASS = NP8 + (RLAST > 1 ? 1 : 0);
-    // column stride (float2) of the padded columns (one pad per 8 elements, see
-    // padi): chosen so that the 8 columns a wave's pass reads and writes touch
-    // 64 distinct banks
-    static constexpr int CS = N1 == 8 ? 10 : N1 == 16 ? 18 : N1 == 32 ? 36 : N1 == 64 ? 72 : N1 == 128 ? 152 : 296;
+    // stride (float2) of the columns (elements at swz) and of the window slots: the LDS serves 16 lanes of an 8-byte access in a cycle, over 32
+    // banks, and these put the 16 -- 8 columns, 2 butterflies or slots -- on
+    // distinct ones
+    static constexpr int CS = N1 == 8 ? 9 : N1 == 32 ? 34 : 66;
+    static constexpr int SS = 32 * CS + (N1 == 8 ? 8 : 0);
+    static_assert(N1 == 8 || N1 == 32 || N1 == 64, "strides for these lengths");
     static constexpr int NBUF = 1;          // column passes run in place
     static constexpr int AP = 72;           // LDS row pitch (FP16) of the DFT-64 rows
     static constexpr int NSPEC = WG / 4;    // channels of column 0 per iteration (FPAR N1)
@@ -98,10 +100,10 @@ constexpr int twb_count(int logn) {
     return n;
 }
 
-// padded position of element j of a column: one pad per 8 elements, which with
-// the column strides above keeps the Stockham reads (consecutive elements) and
-// writes (elements 8 apart) of a wave free of LDS bank conflicts
-__device__ __forceinline__ constexpr int padi(int j) { return j + (j >> 3); }
+// position of element j of a column: neighbours change places in every second
+// group of 8, so that elements 8 apart (a pass's writes) as well as adjacent ones
+// (its reads) fall on distinct banks, and 16 consecutive ones (step 3) fill them
+__device__ __forceinline__ constexpr int swz(int j) { return j ^ ((j >> 3) & 1); }
 
 __device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
@@ -188,7 +190,7 @@ __device__ __forceinline__ void col_pass(const float2 *src, float2 *dst, const f
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[u * R + r] = src[padi(b + BPC * u + r * (N1 / R))];
+        for (int r = 0; r < R; ++r) v[u * R + r] = src[swz(b + BPC * u + r * (N1 / R))];
     }
     if constexpr (C::NBUF == 1 && !LAST) __syncthreads();  // in place: every read before any write
 #pragma unroll
@@ -215,7 +217,7 @@ __device__ __forceinline__ void col_pass(const float2 *src, float2 *dst, const f
             const int k = i & (P - 1);
             const int j = (i - k) * R + k;
 #pragma unroll
-            for (int q = 0; q < R; ++q) dst[padi(j + q * P)] = v[u * R + q];
+            for (int q = 0; q < R; ++q) dst[swz(j + q * P)] = v[u * R + q];
         }
     }
 }
@@ -248,29 +250,24 @@ struct Chan {
     float2 ramp;
     uint32_t q, h;    // INT8/FP8: re and im bytes of the spectra 4j..4j+3 in progress
     uint32_t q0, h0;  // INT8/FP8: those of the first four spectra of the chunk
-    float2 f0;      // FP32: the even spectrum of the pair
+    float2 f0, f1;  // FP32: the pair of spectra
     float pacc;
 };
 
-// Phase, requantisation and corner turn of channel k's value X in spectrum r of
-// the slot; chunk is the channel's 16-byte X-layout chunk of this spectrum group.
+// Phase, requantisation and corner turn of a channel's value X in spectrum r of
+// the slot; the caller stores finished chunks.  FP32: H = 0 the even spectrum of the pair, H = 1 the odd one.
 // INT8 / FP8: the codes go into byte r mod 4 of a pair of words.  H = 0 or 1
 // (the caller knows which half of the chunk spectrum r is in): the first
-// (spectra 0..3 of the chunk) or second (4..7) pair, the chunk stored whole by
-// the caller after its eighth spectrum.  H = -1: the pair in progress, copied
-// aside after the fourth spectrum and the chunk stored here after the eighth.
+// (spectra 0..3 of the chunk) or second (4..7) pair.  H = -1: the second pair,
+// copied to the first after the fourth spectrum.
 template <int BM, int H>
-__device__ __forceinline__ void emit(Chan &c, float2 X, float2 rot, int r, uint32_t bsel, bool active, uint4 *chunk) {
+__device__ __forceinline__ void emit(Chan &c, float2 X, float2 rot, int r, uint32_t bsel) {
     if constexpr (BM == 3) {
         c.pacc += X.x * X.x + X.y * X.y;
         return;
     } else if constexpr (BM == 0) {
         const float2 Y = cmul(cmul(X, c.ramp), rot);
-        if (r & 1) {
-            if (active) *reinterpret_cast<float4 *>(chunk) = make_float4(c.f0.x, c.f0.y, Y.x, Y.y);
-        } else {
-            c.f0 = Y;
-        }
+        (H == 1 ? c.f1 : c.f0) = Y;
     } else {
         uint32_t &q = H == 0 ? c.q0 : c.q, &h = H == 0 ? c.h0 : c.h;
         if constexpr (BM == 1) {
@@ -285,15 +282,10 @@ __device__ __forceinline__ void emit(Chan &c, float2 X, float2 rot, int r, uint3
             q = __builtin_amdgcn_perm(w, q, bsel);
             h = __builtin_amdgcn_perm(w, h, bsel + (1u << (8 * (r & 3))));
         }
-        if constexpr (H < 0) {
-            // a chunk's two halves are stored together (a half written four spectra
-            // before the other leaves L2 twice)
+        if constexpr (H < 0) {  // (a half stored four spectra before the other leaves L2 twice)
             if ((r & 7) == 3) {
                 c.q0 = c.q;
                 c.h0 = c.h;
-            } else if ((r & 7) == 7 && active) {
-                constexpr uint32_t B = BM == 1 ? kI8Bias : 0u;
-                *chunk = make_uint4(c.q0 ^ B, c.q ^ B, c.h0 ^ B, c.h ^ B);
             }
         }
     }
@@ -306,10 +298,6 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     // power cells: 0 none, 1 FP32 |X|^2, 2 FP16 |X|^2 / N^2 -- a template choice, so that a
     // launch without power output carries none of its registers
     constexpr int PW = MODE >> 2;
-    auto store_power = [&](int64_t i, float p) {
-        if constexpr (PW == 1) reinterpret_cast<float *>(a.power)[i] = p;
-        if constexpr (PW == 2) reinterpret_cast<_Float16 *>(a.power)[i] = (_Float16)(p * a.power_scale);
-    };
     constexpr int M = C::M, N = C::N, N1 = C::N1, L = C::L, FPAR = C::FPAR, WG = C::WG;
     constexpr int SPB_MAX = C::SPS * FPAR;
     // spectra per window slot: a power of two, a whole number of chunks (the calibration
@@ -330,7 +318,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     __shared__ __attribute__((aligned(16))) uint32_t lds_x[H16 ? 1 : 2][FPAR][H16 ? 4 : N / 4];
     __shared__ __attribute__((aligned(16))) _Float16 lds_xh[H16 ? FPAR : 1][H16 ? (N / N1) * XP : 8];
     __shared__ __attribute__((aligned(16))) float2 lds_tw[twl_count(C::LOGN1) > 0 ? twl_count(C::LOGN1) : 1];
-    __shared__ __attribute__((aligned(16))) float2 lds_b[C::NBUF][FPAR * 32 * C::CS];
+    __shared__ __attribute__((aligned(16))) float2 lds_b[C::NBUF][FPAR * C::SS];
     __shared__ __attribute__((aligned(16))) uint16_t lds_a[2][64 * C::AP];  // FP16 rows (hi, lo)
     __shared__ __attribute__((aligned(16))) float2 lds_u[FPAR * N1];  // column 0 outputs
     __shared__ float2 lds_rot[SPB_MAX];
@@ -415,10 +403,14 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     static_assert(WG == 256, "four waves per workgroup");
     const int wz = (int)(((uint32_t)blockIdx.x * 0x9E3779B1u) >> 30);
     const int ctid = (tid - 64 * wz) & (WG - 1);
-    const int cp = ctid / C::J;
-    const int cj = ctid % C::J;
+    // Adjacent lanes hold adjacent columns, so that eight lanes store a 128-byte line
+    // of eight channels' chunks (butterflies first, eight lanes stored into eight
+    // lines: FP32 at 64 x 2048 x 8192 1417 us, so 1310).
+    static_assert(C::J == 8, "eight threads per column");
+    const int cp = 8 * (ctid >> 6) + (ctid & 7);
+    const int cj = (ctid >> 3) & 7;
     const int bu = cj / C::BPC, bb = cj % C::BPC;
-    const int colo = (bu * 32 + cp) * C::CS;
+    const int colo = bu * C::SS + cp * C::CS;
     const int nspec_u = ctid / N1, nspec_j = ctid % N1;  // column-0 channel 32 j (ctid < NSPEC)
 
     // ---- output channels of this thread: 8 from column cp (none for cp = 0),
@@ -434,7 +426,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     for (int o = 0; o < 9; ++o) {
         Chan &c = ch[o];
         c.q = c.h = c.q0 = c.h0 = 0u;
-        c.f0 = make_float2(0.f, 0.f);
+        c.f0 = c.f1 = make_float2(0.f, 0.f);
         c.pacc = 0.f;
         const int k = o == 8 ? (ctid < C::NSPEC ? ch_s : 0) : (cp == 0 ? 0 : chan(o));
         // column 0 unfolds 2 X, so its ramp carries the factor 1/2 (exact)
@@ -456,7 +448,9 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     // ---- window fetch: thread t of slot t / L loads bytes 16 (t mod L) .. + 15
     const int fu = tid / L, ft = tid % L;
     const int m_f0 = mblk + sps * fu;  // first spectrum of this thread's fetch slot
-    const bool f_active = m_f0 < a.T;  // T is a multiple of 32
+    // a slot past the last spectrum (T is a multiple of 32) reads the last slot's
+    // windows again, and its chunks are dropped
+    const int m_fetch = min(m_f0, a.T - sps);
     const uint32_t *row = reinterpret_cast<const uint32_t *>(a.x + (int64_t)s * a.row_stride);
     const uint32_t sh = (uint32_t)(D & 3);
     uint32_t pw[5];
@@ -467,23 +461,115 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
         pw[1] = row[w + 1];
         pw[2] = row[w + 2];
         pw[3] = row[w + 3];
-        pw[4] = (o & 3) ? row[w + 4] : 0u;
+        pw[4] = row[w + ((o & 3) ? 4 : 3)];  // an aligned window does not use it
     };
-    if (f_active) fetch(m_f0);
+    fetch(m_fetch);
 
     float2 *lb0 = &lds_b[0][0];
     float2 *lb1 = &lds_b[C::NBUF - 1][0];
     // spectra of the thread's column slot and of its column-0 channel
     const int m_c0 = mblk + sps * bu, m_s0 = mblk + sps * nspec_u;
     const bool c_active = m_c0 < a.T, s_active = m_s0 < a.T;
-    // chunk index of channel k (16-byte units) within a spectrum group
-    auto chunk_base = [&](int k) -> uint32_t {
-        return (uint32_t)((((k >> 3) * a.S + s) << 3) + (k & 7));
+    // Chunks are stored through a buffer resource at the workgroup's first group: a
+    // thread's part of an offset is one of three registers (its lowest channel of the
+    // lower half, its lowest of the upper half, its channel of column 0), the rest
+    // is uniform, and a chunk that is not to be stored has an offset past the buffer,
+    // which the hardware drops.  So every store is issued on every path and none
+    // waits behind a branch.
+    const int group_bytes = M * a.S * 16, k1_bytes = a.S * 1024;  // a spectrum group; 64 channels
+    constexpr int CMAX = C::BPC * (NBL - 1) + (RL - 1) * (N1 / RL);
+    constexpr uint32_t kDrop = 0x80000000u;
+    auto chunk_bytes = [&](int k) -> uint32_t {  // of channel k within a spectrum group
+        return (uint32_t)((((k >> 3) * a.S + s) << 7) + ((k & 7) << 4));
+    };
+    const uint32_t off_lo = c_active && cp != 0 ? (m_c0 - mblk) / G * group_bytes + chunk_bytes(cp + 64 * bb) : kDrop;
+    const uint32_t off_hi =
+        c_active && cp != 0 ? (m_c0 - mblk) / G * group_bytes + chunk_bytes(N - cp - 64 * (bb + CMAX)) : kDrop;
+    const uint32_t off_s =
+        s_active && ctid < C::NSPEC ? (m_s0 - mblk) / G * group_bytes + chunk_bytes(ch_s) : kDrop;
+    const int64_t left = (int64_t)(a.T - mblk) / G * group_bytes;  // bytes from the resource's base to the end
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        static_cast<char *>(a.spec) + (int64_t)(mblk / G) * group_bytes, 0, (int)min(left, (int64_t)1 << 30), 0x00027000);
+    // The whole offset is in a vector register, none of it in the instruction's scalar
+    // offset: with one there the compiler lets the next instruction overwrite the
+    // data registers of a 16-byte store, and this hardware then at times stores
+    // the new value (seen: word 0 of chunks, lanes 8..15 of 16).
+    auto put = [&](f4_uint4 v, uint32_t off) __attribute__((always_inline)) {
+        __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 0);
+    };
+    // the finished chunk of output o (8: that of column 0) of the group before
+    // spectrum r, dropped where there is none
+    constexpr uint32_t B = BM == 1 ? kI8Bias : 0u;
+    auto flush = [&](int o, int r) __attribute__((always_inline)) {
+        const Chan &c = ch[o];
+        const f4_uint4 v = BM == 0 ? f4_uint4{__float_as_uint(c.f0.x), __float_as_uint(c.f0.y), __float_as_uint(c.f1.x),
+                                              __float_as_uint(c.f1.y)}
+                                   : f4_uint4{c.q0 ^ B, c.q ^ B, c.h0 ^ B, c.h ^ B};
+        const uint32_t drop = r < G ? kDrop : 0u;
+        const int g = r < G ? 0 : (r / G - 1) * group_bytes, q = o % RL, co = C::BPC * (o / RL) + q * (N1 / RL);
+        if (o == 8) put(v, (off_s | drop) + (uint32_t)g);
+        else if (q < RL / 2) put(v, (off_lo | drop) + (uint32_t)(g + co * k1_bytes));
+        else put(v, (off_hi | drop) + (uint32_t)(g + (CMAX - co) * k1_bytes));
     };
 
-    // one spectrum r of the slot; H: the half of the INT8 / FP8 chunk it fills
-    auto spectrum = [&](const int r, auto hsel) __attribute__((always_inline)) {
+    // Power cells leave by way of the columns' LDS: a thread's eight channels are 64
+    // apart, so that stored from its registers a wave's cells went out as pieces of
+    // many 128-byte lines.  Each wave puts its cells over its own columns (which
+    // only it reads in the last pass), and in the next spectrum, between two
+    // barriers, the workgroup reads them back in channel order and stores 64
+    // adjacent cells with an instruction; the cells need no more than their own
+    // alignment.  INT8 with FP32 cells at 64 x 4096 x 4096 1470 us from the registers,
+    // 1190 so (without cells 903); FP32 with FP32 cells 2284 and 1692 (1283).
+    // Cell k1 of column cp of window slot u; column 0 holds the channels 32 j at j.
+    // The skews spread a wave's writes and its reads over the banks.
+    float *const lp = reinterpret_cast<float *>(lb0);
+    auto cell = [&](int u, int cp, int k1) -> int {
+        const int skew = N1 == 64 ? cp >> 3 : N1 == 32 ? 4 * u + (cp >> 3) : u >> 2;
+        return 2 * (u * C::SS + cp * C::CS) + skew + k1;
+    };
+    static_assert(2 * C::CS >= N1 + 7, "a column's cells stay in its place");
+    // this thread's part: cells tid + 256 i of the slots' M each, channel tid mod 64
+    // of 64 (its column, and the step to the next 64) in 64-channel block tid / 64 + 4 i
+    const int pch = tid & 63, pcol = pch < 32 ? pch : 64 - pch, pk = tid >> 6;
+    const int pl0 = (pch & 31) == 0 ? 2 * pk + (pch >> 5) : pch < 32 ? pk : N1 - 1 - pk;
+    const int pstep = (pch & 31) == 0 ? 8 : pch < 32 ? 4 : -4;
+    float pcells[PW ? 8 : 1];
+    auto read_power = [&]() __attribute__((always_inline)) {
+        if constexpr (PW != 0) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int u = 256 * i / M, q = i - u * M / 256;
+                pcells[i] = lp[cell(u, (pch & 31) == 0 ? 0 : pcol, pl0 + pstep * q)];
+            }
+        }
+    };
+    auto store_power = [&](int i, int r) __attribute__((always_inline)) {
+        const int u = 256 * i / M, q = i - u * M / 256, m = mblk + sps * u + r;
+        if (m < a.T) {
+            const int64_t at = ((int64_t)s * a.T + m) * M + 256 * q + tid;
+            if constexpr (PW == 1) reinterpret_cast<float *>(a.power)[at] = pcells[i];
+            if constexpr (PW == 2) reinterpret_cast<_Float16 *>(a.power)[at] = (_Float16)(pcells[i] * a.power_scale);
+        }
+    };
+
+    // one spectrum r of the slot; H: the half of the chunk it fills.  FLUSH: the
+    // chunks of the group before go out during it, three at a time between its
+    // steps.  (Stored all at once as their last spectrum is finished, the four waves'
+    // chunks fill the memory pipeline, which drains about 12 bytes a cycle from a
+    // compute unit, and the window loads of the other workgroups queue behind them:
+    // FP32 at 64 x 512 x 32768 1873 us, in threes 1560; at 64 x 2048 x 8192 1506 and 1417.)
+    auto spectrum = [&](const int r, auto hsel, auto fsel) __attribute__((always_inline)) {
         constexpr int H = decltype(hsel)::value;
+        constexpr bool FLUSH = decltype(fsel)::value;
+        auto flush3 = [&](int o) __attribute__((always_inline)) {
+            if constexpr (FLUSH) {
+                if (H >= 0 || (r & 7) == 0) {
+                    flush(o, r);
+                    flush(o + 1, r);
+                    flush(o + 2, r);
+                }
+            }
+        };
         // 1. stage the window bytes (buffer r mod 2: its last reader, stage A two
         //    spectra back, is behind the barriers of the previous spectrum), then
         //    fetch the next window
@@ -501,7 +587,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
             hb[3] = __builtin_amdgcn_perm(0x64646464u, x1, 0x04030402u);
             return __builtin_bit_cast(f4_half8, hb) - (f4_half8)((_Float16)1152.0f);
         };
-        if (f_active) {
+        {
             uint4 d;
             d.x = __builtin_amdgcn_alignbyte(pw[1], pw[0], sh);
             d.y = __builtin_amdgcn_alignbyte(pw[2], pw[1], sh);
@@ -516,8 +602,10 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
                 *reinterpret_cast<uint4 *>(&lds_x[r & 1][fu][4 * ft]) = d;
             }
         }
-        if (f_active && r + 1 < sps) fetch(m_f0 + r + 1);
+        fetch(m_fetch + min(r + 1, sps - 1));
         __syncthreads();
+        flush3(0);
+        if (PW && r) read_power();
         // 2. (*) on the matrix cores: hi and lo twiddle halves into one FP32 sum
         f4_float16 acc = {};
 #pragma unroll
@@ -540,6 +628,13 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
             acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(alo, bf, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(ahi, bf, acc, 0, 0, 0);
         }
+        if constexpr (PW != 0) {
+            if (r) {
+                __syncthreads();  // the cells are read before the columns are written again
+#pragma unroll
+                for (int i = 0; i < 8; ++i) store_power(i, r - 1);
+            }
+        }
         // 3. four-step twiddle, one LDS column per k2; rows k2 = 0 and 32 (column 0)
         //    become the folded real sequence y packed as u[j] = y[2j] + i y[2j + 1]
 #pragma unroll
@@ -547,16 +642,18 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
             const int p = 16 * mt + 4 * (v >> 2) + 2 * hh + ((v & 3) >> 1);
             const float2 A = make_float2(acc[v], acc[v + 1]);
             if (v == 0 && mt == 0 && hh == 0) {
-                float *u0 = reinterpret_cast<float *>(lb0 + (au * 32) * C::CS);
+                float *u0 = reinterpret_cast<float *>(lb0 + au * C::SS);
                 const float y0 = 0.5f * (A.x + A.y), y1 = 0.5f * (A.x - A.y);
-                u0[2 * padi(an1 >> 1) + (an1 & 1)] = y0;
-                u0[2 * padi((an1 >> 1) + N1 / 2) + (an1 & 1)] = y1;
+                u0[2 * swz(an1 >> 1) + (an1 & 1)] = y0;
+                u0[2 * swz((an1 >> 1) + N1 / 2) + (an1 & 1)] = y1;
             } else {
-                lb0[(au * 32 + p) * C::CS + padi(an1)] = cmul(A, tws[v >> 1]);
+                lb0[au * C::SS + p * C::CS + swz(an1)] = cmul(A, tws[v >> 1]);
             }
         }
+        flush3(3);
         // 4. the 32 column transforms
         __syncthreads();
+        flush3(6);
         float2 z[8];
         col_passes<LOGM, 0>(lb0, lb1, lds_tw, colo, bb, z);
         if (cp == 0) {
@@ -567,27 +664,22 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
             }
         }
         // 5-6. phase, requantisation and corner turn of every channel
-        const int mc = m_c0 + r;
         const float2 rot_c = lds_rot[sps * bu + r];
         const uint32_t bsel = (0x03020100u & ~(0xFFu << (8 * (r & 3)))) | (0x04u << (8 * (r & 3)));
-        uint4 *gbase_c = reinterpret_cast<uint4 *>(a.spec) + (int64_t)(mc / G) * M * a.S;
-        if (cp != 0) {
 #pragma unroll
-            for (int o = 0; o < 8; ++o) {
-                const int q = o % RL;
-                const int k = chan(o);
-                const float2 X = q < RL / 2 ? z[o] : make_float2(z[o].x, -z[o].y);
-                if (PW && c_active) store_power(((int64_t)s * a.T + mc) * M + k, X.x * X.x + X.y * X.y);
-                emit<BM, H>(ch[o], X, rot_c, r, bsel, c_active, gbase_c + chunk_base(k));
-            }
+        for (int o = 0; o < 8; ++o) {  // a thread of column 0 computes on, and drops its chunks
+            const int q = o % RL;
+            const float2 X = q < RL / 2 ? z[o] : make_float2(z[o].x, -z[o].y);
+            if (PW && cp != 0)
+                lp[cell(bu, cp, bb + C::BPC * (o / RL) + q * (N1 / RL))] = X.x * X.x + X.y * X.y;
+            emit<BM, H>(ch[o], X, rot_c, r, bsel);
         }
-        // column 0's outputs are written by threads ctid < J and unfolded by threads
-        // ctid < NSPEC, both in wave wz, where the wave's own LDS order suffices
+        // column 0's outputs are written by the threads of column 0 and unfolded by threads
+        // ctid < NSPEC, all in wave wz, where the wave's own LDS order suffices
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         if (ctid < C::NSPEC) {
-            const int ms = m_s0 + r;
             const float2 U = lds_u[nspec_u * N1 + nspec_j];
             const float2 V = lds_u[nspec_u * N1 + ((N1 - nspec_j) & (N1 - 1))];
             const float2 sm = make_float2(U.x + V.x, U.y - V.y), df = make_float2(U.x - V.x, U.y + V.y);
@@ -596,42 +688,48 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
             X.x = fmaf(wsp.x, df.y, fmaf(wsp.y, df.x, sm.x));
             X.y = fmaf(-wsp.x, df.x, fmaf(wsp.y, df.y, sm.y));
             const float2 rot_s = lds_rot[sps * nspec_u + r];
-            uint4 *gbase_s = reinterpret_cast<uint4 *>(a.spec) + (int64_t)(ms / G) * M * a.S;
             // column 0 unfolds 2 X: power and the calibration sum take |X|^2 = |2 X|^2 / 4
             if constexpr (BM != 3) {
-                if (PW && s_active) store_power(((int64_t)s * a.T + ms) * M + ch_s, 0.25f * (X.x * X.x + X.y * X.y));
-                emit<BM, H>(ch[8], X, rot_s, r, bsel, s_active, gbase_s + chunk_base(ch_s));
+                if (PW) lp[cell(nspec_u, 0, nspec_j)] = 0.25f * (X.x * X.x + X.y * X.y);
+                emit<BM, H>(ch[8], X, rot_s, r, bsel);
             } else {
                 ch[8].pacc += 0.25f * (X.x * X.x + X.y * X.y);
             }
         }
     };
+    using std::integral_constant;
     if constexpr ((BM == 1 || BM == 2) && PW == 0) {
         // spectra in chunks of 8: the first 4 fill one pair of words, the next 4
-        // the other (which pair is a constant of each loop), then every chunk is
-        // stored whole.  (With power cells the copy of the loop body for each
-        // half does not fit the registers; those launches keep one loop.)
-        constexpr uint32_t B = BM == 1 ? kI8Bias : 0u;
+        // the other (which pair is a constant of each loop).  (With power cells the
+        // copy of the loop body for each half does not fit the registers; those
+        // launches keep one loop.)
 #pragma unroll 1
         for (int r8 = 0; r8 < sps; r8 += 8) {
+            spectrum(r8, integral_constant<int, 0>{}, std::true_type{});
 #pragma unroll 1
-            for (int r = r8; r < r8 + 4; ++r) spectrum(r, std::integral_constant<int, 0>{});
+            for (int r = r8 + 1; r < r8 + 4; ++r) spectrum(r, integral_constant<int, 0>{}, std::false_type{});
 #pragma unroll 1
-            for (int r = r8 + 4; r < r8 + 8; ++r) spectrum(r, std::integral_constant<int, 1>{});
-            if (cp != 0 && c_active) {
-                uint4 *gb = reinterpret_cast<uint4 *>(a.spec) + (int64_t)((m_c0 + r8) / G) * M * a.S;
-#pragma unroll
-                for (int o = 0; o < 8; ++o)
-                    gb[chunk_base(chan(o))] = make_uint4(ch[o].q0 ^ B, ch[o].q ^ B, ch[o].h0 ^ B, ch[o].h ^ B);
-            }
-            if (ctid < C::NSPEC && s_active) {
-                uint4 *gb = reinterpret_cast<uint4 *>(a.spec) + (int64_t)((m_s0 + r8) / G) * M * a.S;
-                gb[chunk_base(ch_s)] = make_uint4(ch[8].q0 ^ B, ch[8].q ^ B, ch[8].h0 ^ B, ch[8].h ^ B);
-            }
+            for (int r = r8 + 4; r < r8 + 8; ++r) spectrum(r, integral_constant<int, 1>{}, std::false_type{});
+        }
+    } else if constexpr (BM == 0) {
+#pragma unroll 1
+        for (int r = 0; r < sps; r += 2) {  // pairs of spectra, one chunk per channel
+            spectrum(r, integral_constant<int, 0>{}, std::true_type{});
+            spectrum(r + 1, integral_constant<int, 1>{}, std::false_type{});
         }
     } else {
 #pragma unroll 1
-        for (int r = 0; r < sps; ++r) spectrum(r, std::integral_constant<int, -1>{});
+        for (int r = 0; r < sps; ++r) spectrum(r, integral_constant<int, -1>{}, integral_constant<bool, BM != 3>{});
+    }
+    if constexpr (BM != 3) {  // the last group's chunks
+#pragma unroll
+        for (int o = 0; o < 9; ++o) flush(o, sps);
+    }
+    if constexpr (PW != 0) {  // the last spectra's cells
+        __syncthreads();
+        read_power();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) store_power(i, sps - 1);
     }
 
     if constexpr (BM == 3) {

@@ -1,0 +1,42 @@
+"""The four-step F-engine's power cells leave through LDS in channel order: every
+cell of every slot, at an address aligned to one cell only, and nothing beside them."""
+import numpy as np
+import pytest
+
+import paper_0910_1517_amd as corr
+import synth
+from gpu_util import geom_dev, row_stride_for
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("half", [0, 1])
+@pytest.mark.parametrize("prec", [corr.FP32, corr.INT8, corr.FP8_E4M3])
+@pytest.mark.parametrize("N,T", [(512, 32), (512, 416), (2048, 32), (2048, 96), (4096, 32), (4096, 160)])
+def test_cells_are_the_spectra_squared(N, T, prec, half):
+    import torch
+    S, C = 3, N // 2
+    g = geom_dev(synth.make_geometry(2, seed=N).subset(np.arange(S)))
+    rs = row_stride_for(N, T, 16)
+    gen = torch.Generator(device="cuda").manual_seed(N + T)
+    x = torch.randint(-127, 128, (S, rs), generator=gen, device="cuda", dtype=torch.int8)
+
+    plan = corr.Plan(S, N, T, precision=corr.FP32)
+    spec = plan.alloc("spectra", zero=False)
+    plan.fengine(x, g, spec, None, row_stride=rs, spectrum0=3)
+    y = spec.view(torch.float32).view(T // 2, C // 8, S, 8, 2, 2)  # [g][k/8][s][k%8][t%2][re im]
+    want = (y.double() ** 2).sum(-1).permute(2, 0, 4, 1, 3).reshape(S, T, C)
+
+    plan = corr.Plan(S, N, T, precision=prec, power_fp16=half)
+    scale = torch.full((S, C), 30.0, device="cuda") if prec != corr.FP32 else None
+    pad = torch.full((S * T * C + 2,), -1.0, device="cuda", dtype=torch.float16 if half else torch.float32)
+    plan.fengine(x, g, plan.alloc("spectra", zero=False), scale, power=pad[1:-1], row_stride=rs, spectrum0=3)
+    assert pad[0] == -1 and pad[-1] == -1
+    got = pad[1:-1].view(S, T, C).double()
+    # |Y|^2 of the phased FP32 spectra against |X|^2: two rotations and the two squares, a
+    # few 2^-24 each; FP16 cells round |X|^2 / N^2 to 2^-11, or to 2^-25 below 2^-14
+    if half:
+        want = want / N ** 2
+        assert ((got - want).abs() <= want * (2.0 ** -11 + 2e-6) + 2.0 ** -25).all()
+    else:
+        assert ((got - want).abs() <= want * 2e-6).all()
