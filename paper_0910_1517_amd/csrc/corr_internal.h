@@ -113,17 +113,22 @@ __device__ __forceinline__ void put_power(const FLaunch &a, int64_t i, float p) 
 }
 
 // Which F-engine serves a launch: the four-step (matrix-core) one at log2 M =
-// 8, 10 and 11 outside table mode (launch modes 0-3), the LDS-radix one
-// (fengine.hip) otherwise.  The choice is measured: 64 signals of 2^27
-// samples, int8 output, ms per call
-//   log2 M         8      9      10     11     12
-//   four-step    7.99  10.20   9.40   9.64  15.92
-//   LDS-radix    9.05   9.28  10.35  10.69  12.12
-// (FP32 output: the four-step kernel 2-15% faster at 8-11, 10% slower at 12;
-// table mode at 11: 14.7 against 12.0 ms); at 13 the four-step kernel spills
-// registers.
-constexpr bool use_fengine4(int log2m, int mode) {
-    return mode < 4 && (log2m == 8 || log2m == 10 || log2m == 11);
+// 8, 10 and 11 outside table mode (launch modes 0-3) and, for FP32 spectra without
+// power cells, at 9; the LDS-radix one (fengine.hip) otherwise.  The choice is
+// measured, 64 signals of 2^24 samples, us per call:
+//   log2 M                      8     9     10    11    12
+//   int8 output: four-step     765   876   884   901
+//                LDS-radix    1077  1094  1272  1308  1490
+//   FP32 output: four-step    1507  1316  1303  1282
+//                LDS-radix    1671  1703  1817  1879  1949
+// At 9 the four-step kernel rounds differently from the LDS-radix one, which has
+// always served that length: FP32 spectra are a little nearer to 64 bits (1.385e-7
+// against 1.412e-7; noise of one bit to full scale and tones 2 to 8% less), but
+// codes, scales and flags taken from power cells would change, so those stay.  At 12
+// and 13 a window is 512 threads or more, two workgroups a compute unit, and at 13
+// the four-step kernel spills registers.
+constexpr bool use_fengine4(int log2m, int mode, bool power) {
+    return mode < 4 && (log2m == 8 || log2m == 10 || log2m == 11 || (log2m == 9 && mode == 0 && !power));
 }
 
 // Phase look-up table of section 2.3.2: 1440 steps of 0.25 degrees.

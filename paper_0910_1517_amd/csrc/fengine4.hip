@@ -83,9 +83,9 @@ struct F4Cfg {
     // stride (float2) of the columns (elements at swz) and of the window slots: the LDS serves 16 lanes of an 8-byte access in a cycle, over 32
     // banks, and these put the 16 -- 8 columns, 2 butterflies or slots -- on
     // distinct ones
-    static constexpr int CS = N1 == 8 ? 9 : N1 == 32 ? 34 : 66;
+    static constexpr int CS = N1 == 8 ? 9 : N1 + 2;
     static constexpr int SS = 32 * CS + (N1 == 8 ? 8 : 0);
-    static_assert(N1 == 8 || N1 == 32 || N1 == 64, "strides for these lengths");
+    static_assert(N1 == 8 || N1 == 16 || N1 == 32 || N1 == 64, "strides for these lengths");
     static constexpr int NBUF = 1;          // column passes run in place
     static constexpr int AP = 72;           // LDS row pitch (FP16) of the DFT-64 rows
     static constexpr int NSPEC = WG / 4;    // channels of column 0 per iteration (FPAR N1)
@@ -759,15 +759,22 @@ hipError_t launch4_one(int mode, FLaunch a, hipStream_t st) {
     const int nblk = (a.T + spb - 1) / spb;
     const dim3 grid(a.S * nblk), block(C::WG);
     const int pw = (mode == 3 || !a.power) ? 0 : (a.power_f16 ? 2 : 1);
-    switch (mode | (pw << 2)) {
 #define F4_CASE(m) \
     case m: hipLaunchKernelGGL((fengine4_kernel<LOGM, m>), grid, block, 0, st, a); break;
-    F4_CASE(0) F4_CASE(1) F4_CASE(2) F4_CASE(3)     // no power cells
-    F4_CASE(4) F4_CASE(5) F4_CASE(6)                // FP32 power
-    F4_CASE(8) F4_CASE(9) F4_CASE(10)               // FP16 power
-#undef F4_CASE
-    default: return hipErrorInvalidValue;
+    if constexpr (LOGM == 9) {  // FP32 spectra alone (use_fengine4)
+        switch (mode | (pw << 2)) {
+        F4_CASE(0)
+        default: return hipErrorInvalidValue;
+        }
+    } else {
+        switch (mode | (pw << 2)) {
+        F4_CASE(0) F4_CASE(1) F4_CASE(2) F4_CASE(3)     // no power cells
+        F4_CASE(4) F4_CASE(5) F4_CASE(6)                // FP32 power
+        F4_CASE(8) F4_CASE(9) F4_CASE(10)               // FP16 power
+        default: return hipErrorInvalidValue;
+        }
     }
+#undef F4_CASE
     return hipGetLastError();
 }
 
@@ -826,6 +833,7 @@ void fengine4_tables(int log2m, uint16_t *afrag, float2 *tw4, float2 *twb, size_
 hipError_t launch_fengine4(int log2m, int mode, const FLaunch &a, hipStream_t st) {
     switch (log2m) {
     case 8: return launch4_one<8>(mode, a, st);
+    case 9: return launch4_one<9>(mode, a, st);
     case 10: return launch4_one<10>(mode, a, st);
     case 11: return launch4_one<11>(mode, a, st);
     default: return hipErrorInvalidValue;  // the other lengths run on the LDS-radix kernel
