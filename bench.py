@@ -41,8 +41,8 @@ CONFIGS = {
 }
 HBM_PEAK = 8.0e12           # B/s
 INT8_PEAK = 5.0e15          # dense int8 MFMA OP/s
-FP32_MFMA_PEAK = 157.3e12   # dense FP32 matrix FLOP/s
-FP16_MFMA_PEAK = 2.5e15     # dense FP16 matrix FLOP/s
+FP16_MFMA_PEAK = 2.5e15     # dense FP16 (and BF16) matrix FLOP/s
+FP32_X_PEAK = FP16_MFMA_PEAK / 6  # the FP32 X-engine's: six BF16 products for an FP32 one
 CNN_FLOP_PER_CELL = 2 * (16 * 9 + 16 * 16 * 9 + 16 * 9)  # 2592 MACs of the three 3x3 layers
 # FP32 vector peak without packed-FP32 instructions (which this library never
 # emits): 256 CUs x 4 SIMDs x 16 lanes x 2 flops (FMA) x 2.4 GHz.  The 157.3
@@ -54,36 +54,35 @@ FP32_PUBLISHED_PEAK = 157.3e12  # the datasheet's FP32 vector figure (packed FP3
 # calibration copy, see profiles/), valid only for the kernel source they were
 # taken from: reported as `traffic` when the source hash still matches.
 MEASURED_TRAFFIC = {
-    # profiles/fx_int8_64sig_4096pt_32768spec.md: FETCH_SIZE 4468485 KiB x 2.000, WRITE_SIZE 8388932 KiB x 1.000
-    # (medians of 7 dispatches, with the source's instruction-level-parallelism schedule)
+    # profiles/fx_int8_64sig_4096pt_32768spec.md: FETCH_SIZE 4471217 KiB x 2.000, WRITE_SIZE 8388671 KiB x 1.000
+    # (medians of 9 dispatches, with the source's instruction-level-parallelism schedule)
     "fengine_int8_c3": {"source": "paper_0910_1517_amd/csrc/fengine4.hip",
-                        "sha256": "59ba376590687bfeb9bf11ebeabfc7cccdfdcc610893e4b27ca29d0f09025fda",
+                        "sha256": "ea1e5adf8c00e3dc987735b3db58ae458b567cd3d8fb5ecf0376f32bb6586bfb",
                         "flags": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-                        "read": 9.151e9, "write": 8.590e9},
-    # profiles/fx_fp32_64sig_1024pt_16384spec_pointsources.md: FETCH_SIZE 537802 KiB x 2.000, WRITE_SIZE 4194304 KiB
+                        "read": 9.157e9, "write": 8.590e9},
+    # profiles/fx_fp32_64sig_1024pt_16384spec_pointsources.md: FETCH_SIZE 531970 KiB x 2.000, WRITE_SIZE 4337386 KiB
     # (medians of 6 dispatches)
-    "fengine_fp32_c2": {"source": "paper_0910_1517_amd/csrc/fengine.hip",
-                        "sha256": "752cc90ed275dea5e3ee47a0f95cb1472859c15dff0c235504cf6068a8a8039a",
-                        "flags": [],
-                        "read": 1.101e9, "write": 4.295e9},
+    "fengine_fp32_c2": {"source": "paper_0910_1517_amd/csrc/fengine4.hip",
+                        "sha256": "ea1e5adf8c00e3dc987735b3db58ae458b567cd3d8fb5ecf0376f32bb6586bfb",
+                        "flags": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-sched-strategy=max-ilp"],
+                        "read": 1.089e9, "write": 4.441e9},
     # profiles/cnn_flagged_64sig_8192pt_8192spec.md (FP16 power, column guard, max-ilp schedule): FETCH_SIZE
-    # 2097368 KiB x 2.000, WRITE_SIZE 2097152 KiB
+    # 2097369 KiB x 2.000, WRITE_SIZE 2097152 KiB
     "cnn_infer_c5": {"source": "paper_0910_1517_amd/csrc/cnn.hip",
-                     "sha256": "262fd32417682dd772bc249c879504260bc82e884cae8115691124ba211a5e03",
+                     "sha256": "9c4e9f80b169dae3d8328ccca04a131c7b44aab6a0f9f6e062d3cd1ccd282e1d",
                      "flags": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
                      "read": 4.295e9, "write": 2.147e9},
     # profiles/fx_int8_64sig_4096pt_32768spec.md: FETCH_SIZE 4197483 KiB x 2.000, WRITE_SIZE 1572864 KiB x 1.000
     "beam_int8_c3": {"source": "paper_0910_1517_amd/csrc/beam.hip",
                      "sha256": "fdea2c6b6d608a65e64c732609303dc9d4f9377b18ad830e8b407f4c35843b4f",
                      "read": 8.597e9, "write": 1.611e9},
-    # profiles/blank_int8_64sig_134Msamples.md: out of place FETCH_SIZE 4211175 KiB x 2.000, WRITE_SIZE 9624595 KiB
+    # profiles/blank_int8_64sig_134Msamples.md: out of place FETCH_SIZE 4211137 KiB x 2.000, WRITE_SIZE 8520888 KiB
     "blank_out_c3": {"source": "paper_0910_1517_amd/csrc/blank.hip",
-                     "sha256": "3d7db02ee39e54f695df0e2e89e58bb8292bdfc262d90a9c60d3e880341b0b8b",
-                     "read": 8.624e9, "write": 9.856e9},
-    # same profile, in place: FETCH_SIZE 4211023 KiB x 2.000, WRITE_SIZE 900710 KiB.  (Both blank.hip records
-    # follow host-side and comment changes whose device code compiles to the same instructions.)
+                     "sha256": "0f09cbd71dbe95a51c5f6e8a2c92a094a331ac9e00aaf0e0b11e760ee0127ff8",
+                     "read": 8.624e9, "write": 8.725e9},
+    # same profile, in place: FETCH_SIZE 4211154 KiB x 2.000, WRITE_SIZE 900717 KiB
     "blank_in_c3": {"source": "paper_0910_1517_amd/csrc/blank.hip",
-                    "sha256": "3d7db02ee39e54f695df0e2e89e58bb8292bdfc262d90a9c60d3e880341b0b8b",
+                    "sha256": "0f09cbd71dbe95a51c5f6e8a2c92a094a331ac9e00aaf0e0b11e760ee0127ff8",
                     "read": 8.624e9, "write": 0.922e9},
 }
 
@@ -836,9 +835,9 @@ def main():
     if gmrt:
         tf, tx = r32["t_f"], r32["t_x"]
         f_part = f_roof(tf, ff32, fb32, "%s (FP32 F-engine)" % r32["fkernel"])
-        x_part = {"kernel": "xengine_kernel<2, 0> (FP32 MFMA X-engine)", "bound": "mfma",
-                  "achieved": round(xops32 / tx / 1e12, 3), "peak": FP32_MFMA_PEAK / 1e12, "unit": "TFLOP/s",
-                  "frac": round(xops32 / tx / FP32_MFMA_PEAK, 4), "hbm_gbs": round(xin32 / tx / 1e9, 1)}
+        x_part = {"kernel": "xengine_kernel<2, 0> (FP32 X-engine, three BF16 parts a value)", "bound": "mfma",
+                  "achieved": round(xops32 / tx / 1e12, 3), "peak": round(FP32_X_PEAK / 1e12, 1), "unit": "TFLOP/s",
+                  "frac": round(xops32 / tx / FP32_X_PEAK, 4), "hbm_gbs": round(xin32 / tx / 1e9, 1)}
         dom = f_part if tf >= tx else x_part
         traffic = measured_traffic("fengine_fp32_c2") if tf >= tx else None
     else:
@@ -899,7 +898,7 @@ def main():
         out["fp32"] = {"correlated_bandwidth_mhz": round(bw(t32), 3), "ms_per_step": round(t32 * 1e3, 4),
                        "x_engine_tops": round(xops32 / r32["t_x"] / 1e12, 3),
                        "ms": {k: round(v * 1e3, 4) for k, v in r32.items() if k.startswith("t_")},
-                       "x_mfma_frac_algorithmic": round(xops32 / r32["t_x"] / FP32_MFMA_PEAK, 4),
+                       "x_mfma_frac_algorithmic": round(xops32 / r32["t_x"] / FP32_X_PEAK, 4),
                        "x_splits": r32["splits"], "graph_matches_eager": r32.get("graph_matches_eager")}
         out["int8_vs_fp32_speedup"] = round(t32 / t8, 3)
     if r8f:

@@ -64,7 +64,7 @@ typedef int32_t corr_status;
 #define CORR_ERR_IO (-11)         /* file could not be opened, read or written  */
 
 /* Arithmetic of the spectra handed from the F- to the X-engine. */
-#define CORR_FP32 0     /* complex64 spectra, FP32 MFMA X-engine                */
+#define CORR_FP32 0     /* complex64 spectra, FP32-accurate BF16 MFMA X-engine   */
 #define CORR_INT8 1     /* int8 (re, im) in [-127, 127], int8 MFMA, int32 sums  */
 #define CORR_FP8_E4M3 2 /* OCP e4m3 (re, im), FP8 MFMA, FP32 sums               */
 

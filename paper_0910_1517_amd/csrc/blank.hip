@@ -30,8 +30,9 @@
 // block, turned into the integer range [lo, hi] of values kept.  The blanked
 // positions of a block are queued in LDS, and all lanes then compute their
 // replacements from the table in FP64 and store them as single bytes.  Out of
-// place, the block is copied right after it is loaded and the replacements patch
-// the copy; in place, only the blanked bytes are written.
+// place, the block is copied (where the registers hold it that long, just before
+// the replacements) and they patch the copy; in place, only the blanked bytes are
+// written.
 //
 // Noise table: entry j of signal s is the Irwin-Hall sum of twelve 16-bit
 // uniforms (U + 1/2) / 65536, minus 6.  The uniforms are the 16-bit halves
