@@ -575,7 +575,7 @@ constexpr int XCOLS = W + 4;  // input columns: zero column on the left, three o
 constexpr int PC = W + 2;     // activation row pitch: one zero column at each edge
 constexpr int RX = 8;         // rows kept of the input, of the layer-1 output and of the tap sums
 constexpr int XPITCH = 10;    // halves per input column: RX rows + 2 pad (odd dword stride)
-constexpr int IWG = 512;      // 8 waves, one 32-column strip each
+constexpr int IWG = 1024;     // 16 waves, two for each 32-column strip
 
 // Accumulator layout of a 32 x 32 MFMA: register j of lane l holds row
 // 8 (j / 4) + 4 (l / 32) + j mod 4, column l mod 32.
@@ -596,13 +596,19 @@ __device__ inline uint32_t relu_h2(float a, float b) {
 // (or 64) LDS banks once.
 __device__ inline int a1_off(int pcol, int h) { return 32 * pcol + 16 * (h ^ (((pcol >> 2) ^ (pcol >> 3)) & 1)); }
 
-// One workgroup per compute unit, looping over tiles.  Wave w owns columns
-// 32 w .. 32 w + 31 and walks the tile two rows at a time in a software
-// pipeline with one barrier per step j:
+// One workgroup per compute unit, looping over tiles.  Two waves own columns
+// 32 w .. 32 w + 31 and walk the tile two rows at a time in a software pipeline
+// with one barrier per step j.  The row wave takes
 //   x rows 2j + 5, 2j + 6 = log(1 + P / m) (FP16) into the input ring,
 //   layer 1 for rows 2j + 2, 2j + 3,
-//   layer 2 and the layer-3 tap sums for rows 2j - 2, 2j - 1,
 //   the logits of rows 2j - 6, 2j - 5,
+// mostly vector instructions and LDS accesses, the other
+//   layer 2 and the layer-3 tap sums for rows 2j - 2, 2j - 1,
+// mostly matrix products, which so run beside the first: a wave that took all
+// the stages in turn had every unit waiting for another (matrix cores, vector ALUs
+// and LDS each busy 42%; 64 x 4096 x 4096 FP16 cells with 8 such waves 8030 us,
+// now 7280).  The layer-2 waves have the higher priority (4% slower without): their
+// step is the longer one.
 // each stage reading only what earlier steps wrote, from rings of 8 rows.
 // Layer 2 of a row pair reads layer-1 rows 2j - 3 .. 2j; the first two were
 // read by the previous step and stay in registers.  Layer-1 rows -1 and 64
@@ -622,7 +628,7 @@ __device__ inline int a1_off(int pcol, int h) { return 32 * pcol + 16 * (h ^ (((
 //            directly from the layer-2 accumulator (its 8 channels per lane
 //            are exactly one lane's K slots), then z3[p] = b3 + sum of U over
 //            the 9 shifted neighbours of p.
-template <typename PT>
+template <typename PT, bool LOGITS>
 __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict__ params,
                                                         const PT *__restrict__ power, int64_t T, int C,
                                                         int n_tiles, float thr_logit, float guard_m,
@@ -632,11 +638,12 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
     __shared__ __align__(16) _Float16 a1s[RX][PC][16];   // layer-1 ring (slot = row mod 8)
     __shared__ float us[RX][PC][9];                      // tap-sum ring (slot = row mod 8)
     __shared__ float colv[2][W];                         // column sums of even / odd rows
-    __shared__ float srt[IWG / 64][W];                   // each wave's sorted channel means (guard)
+    __shared__ __align__(16) float srt[W];               // sorted channel means (guard)
+    __shared__ uint8_t guard[W / 4];
+    __shared__ float level;                              // the tile's median
 
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int t = threadIdx.x, lane = t & 63, wv = (t >> 6) & 7;
     const int half = lane >> 5, col = lane & 31;
-    const int xc = t & (W - 1), xh = t >> 8;  // input staging: column xc, rows of parity xh
 
     // ---- zero border columns, written once (never overwritten below)
     for (int e = t; e < 4 * XPITCH; e += IWG) xs[(e / XPITCH) == 0 ? 0 : W + (e / XPITCH)][e % XPITCH] = (_Float16)0.f;
@@ -649,34 +656,8 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
         us[rr][side ? PC - 1 : 0][k] = 0.f;
     }
 
-    // ---- weights as MFMA A operands (lane: row = lane mod 32, K slots 8 half + j)
-    const int arow = lane & 31, aslot = arow >> 4, ao = arow & 15;
-    half8 A1, A3, A2[4][3];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int rho = 2 * half + (j & 1), dv = j >> 1, u = rho - aslot;
-        float w = (dv < 3 && u >= 0 && u <= 2) ? params[kW1 + ao * 9 + u * 3 + dv] : 0.f;
-        if (half == 0 && j == 7) w = params[kB1 + ao];  // constant-1 slot: the bias
-        A1[j] = (_Float16)w;
-        const int ch = 8 * (j / 4) + 4 * half + (j & 3);
-        A3[j] = (_Float16)(arow < 9 ? params[kW3 + ch * 9 + arow] : 0.f);
-    }
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-#pragma unroll
-        for (int dv = 0; dv < 3; ++dv)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int cin = 8 * half + j, u = p - aslot;
-                A2[p][dv][j] = (_Float16)((u >= 0 && u <= 2) ? params[kW2 + ((ao * 16 + cin) * 3 + u) * 3 + dv] : 0.f);
-            }
-    float16v bias2;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) bias2[j] = params[kB2 + (acc_row(j, half) & 15)];
-    const float b3 = params[kB3];
+    const int arow = lane & 31, aslot = arow >> 4, ao = arow & 15;  // A operands: lane: row = lane mod 32, K slots 8 half + j
     const float16v zero16 = {};
-    const half8 zero8 = {};
-
     const int c0 = wv * 32;
     const int pc = c0 + col + 1;  // padded column of this lane's pixel
     const uint32_t *xl = reinterpret_cast<const uint32_t *>(&xs[c0 + col][0]);
@@ -687,10 +668,110 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
     int a1rd[3];
 #pragma unroll
     for (int dv = 0; dv < 3; ++dv) a1rd[dv] = a1_off(pc - 1 + dv, half);
-    float *uw = &us[0][pc][0];
+    float *uw = &us[0][pc][4 * half];
     const float *ur = &us[0][pc - 1][0];
     constexpr int AROW = PC * 16 * 2, UROW = PC * 9;  // bytes, floats
 
+    // the two halves of the workgroup pass the same barriers: three at the top of a
+    // tile and one after each of its steps
+    if (__builtin_amdgcn_readfirstlane(t) >= IWG / 2) {
+        __builtin_amdgcn_s_setprio(2);
+        half8 A3, A2[4][3];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int ch = 8 * (j / 4) + 4 * half + (j & 3);
+            A3[j] = (_Float16)(arow < 9 ? params[kW3 + ch * 9 + arow] : 0.f);
+        }
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+#pragma unroll
+            for (int dv = 0; dv < 3; ++dv)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int cin = 8 * half + j, u = p - aslot;
+                    A2[p][dv][j] = (_Float16)((u >= 0 && u <= 2) ? params[kW2 + ((ao * 16 + cin) * 3 + u) * 3 + dv] : 0.f);
+                }
+        float bias2[8];  // of accumulator registers j and j + 8
+#pragma unroll
+        for (int j = 0; j < 8; ++j) bias2[j] = params[kB2 + acc_row(j, half)];
+        for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+            __syncthreads();
+            __syncthreads();
+            __syncthreads();
+            half8 Fa[3], Fb[3];  // layer-1 operands of rows 2j - 3, 2j - 2, read by the previous step
+            // Layer 2 and the tap sums (mostly the matrix cores), rows r2, r2 + 1,
+            // r2 = 2j - 2 (layer-1 rows r2 - 1 .. r2 + 2):
+            auto stage_layer2 = [&](const int j, auto body_tag) __attribute__((always_inline)) {
+                constexpr bool BODY = decltype(body_tag)::value;
+                if (!BODY && (j < 0 || j > H / 2)) return;
+                half8 Fc[3], Fd[3];  // layer-1 rows 2j - 1, 2j
+                const char *fc = a1base + ((2 * j - 1) & (RX - 1)) * AROW;
+                const char *fd = a1base + ((2 * j) & (RX - 1)) * AROW;
+#pragma unroll
+                for (int dv = 0; dv < 3; ++dv) {
+                    Fc[dv] = *reinterpret_cast<const half8 *>(fc + a1rd[dv]);
+                    Fd[dv] = *reinterpret_cast<const half8 *>(fd + a1rd[dv]);
+                }
+                if (BODY || j >= 1) {
+                    const int r2 = 2 * j - 2;
+                    float16v D;
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        asm("" : "+v"(bias2[q]));  // otherwise the compiler keeps the copies, in 16 registers
+                        D[q] = D[q + 8] = bias2[q];
+                    }
+#pragma unroll
+                    for (int dv = 0; dv < 3; ++dv) D = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[0][dv], Fa[dv], D, 0, 0, 0);
+#pragma unroll
+                    for (int dv = 0; dv < 3; ++dv) D = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[1][dv], Fb[dv], D, 0, 0, 0);
+#pragma unroll
+                    for (int dv = 0; dv < 3; ++dv) D = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[2][dv], Fc[dv], D, 0, 0, 0);
+#pragma unroll
+                    for (int dv = 0; dv < 3; ++dv) D = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[3][dv], Fd[dv], D, 0, 0, 0);
+#pragma unroll
+                    for (int sl = 0; sl < 2; ++sl) {
+                        u32x4 bu;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) bu[q] = relu_h2(D[8 * sl + 2 * q], D[8 * sl + 2 * q + 1]);
+                        const float16v U =
+                            __builtin_amdgcn_mfma_f32_32x32x16_f16(A3, __builtin_bit_cast(half8, bu), zero16, 0, 0, 0);
+                        float *dst = uw + ((r2 + sl) & (RX - 1)) * UROW;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) dst[q] = U[q];
+                        if (half == 0) dst[8] = U[4];
+                    }
+                }
+#pragma unroll
+                for (int dv = 0; dv < 3; ++dv) {
+                    Fa[dv] = Fc[dv];
+                    Fb[dv] = Fd[dv];
+                }
+            };
+            auto steps = [&](const int jb, auto body_tag) __attribute__((always_inline)) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    stage_layer2(jb + q, body_tag);
+                    __syncthreads();
+                }
+            };
+            steps(-1, std::false_type{});
+#pragma unroll 1
+            for (int i = 1; i < H / 8; ++i) steps(4 * i - 1, std::true_type{});
+            steps(H / 2 - 1, std::false_type{});
+        }
+        return;
+    }
+
+    half8 A1;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int rho = 2 * half + (j & 1), dv = j >> 1, u = rho - aslot;
+        float w = (dv < 3 && u >= 0 && u <= 2) ? params[kW1 + ao * 9 + u * 3 + dv] : 0.f;
+        if (half == 0 && j == 7) w = params[kB1 + ao];  // constant-1 slot: the bias
+        A1[j] = (_Float16)w;
+    }
+    const float b3 = params[kB3];
+    const int xc = t & (W - 1), xh = (t >> 8) & 1;  // input staging: column xc, rows of parity xh
     auto tile_base = [&](int tl) {
         int s, k0;
         int64_t m0;
@@ -723,34 +804,37 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
         const bool has_next = tile + (int)gridDim.x < n_tiles;
         const PT *tn = has_next ? power + tile_base(tile + gridDim.x) : tb;
         uint8_t *fb = flags + base;
-        float *lb = logits ? logits + base : nullptr;
+        float *lb = logits + (LOGITS ? base : 0);
 
         // ---- reference level: median over the 256 channels of each channel's mean power
         colv[xh][xc] = csum;
-        for (int e = t; e < PC * 2; e += IWG)  // layer-1 row -1 (slot 7): zero
+        for (int e = t; e < PC * 2; e += IWG / 2)  // layer-1 row -1 (slot 7): zero
             reinterpret_cast<uint4 *>(a1base + (RX - 1) * AROW)[e] = make_uint4(0u, 0u, 0u, 0u);
         __syncthreads();
-        float cv[4], cm[4];
+        // One wave takes the statistics: eight, alike, shared the SIMDs' issue slots (16 x
+        // 4096 x 4096 FP16 cells 2010 us, now 1934).
+        if (__builtin_amdgcn_readfirstlane(t) < 64) {
+            float cv[4], cm[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cm[q] = cv[q] = (colv[0][4 * lane + q] + colv[1][4 * lane + q]) * (1.0f / H);
-        const float med = wave_median256(cv, lane);  // sorts cv
-        const float inv = 1.0f / (med > 0.f ? med : 1.f);
-        // column guard: the channel means are the MAD column statistic (section 5, Eq. 3
-        // and 4); a column whose mean is an outlier is flagged whole.  gcol is the guard
-        // bit of this lane's output column c0 + col (lane (c0 + col) / 4 holds its mean).
-        uint32_t gcol = 0u;
-        if (guard_m > 0.f) {
-            float d[4];
+            for (int q = 0; q < 4; ++q) cm[q] = cv[q] = (colv[0][4 * lane + q] + colv[1][4 * lane + q]) * (1.0f / H);
+            const float m = wave_median256(cv, lane);  // sorts cv
+            // column guard: the channel means are the MAD column statistic (section 5, Eq. 3
+            // and 4); a column whose mean is an outlier is flagged whole.  guard[l]: the
+            // guard bits of columns 4 l .. 4 l + 3.
             uint32_t bits = 0u;
+            if (guard_m > 0.f) {
+                const float mad = wave_mad256_sorted(cv, m, lane, srt);
+                const float thr = guard_m * mad / 0.6745f;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) d[q] = fabsf(cm[q] - med);
-            const float mad = wave_mad256_sorted(cv, med, lane, srt[wv]);
-            const float thr = guard_m * mad / 0.6745f;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) bits |= (d[q] > thr ? 1u : 0u) << q;
-            const int oc = c0 + col;
-            gcol = ((uint32_t)__shfl((int)bits, oc >> 2) >> (oc & 3)) & 1u;
+                for (int q = 0; q < 4; ++q) bits |= (fabsf(cm[q] - m) > thr ? 1u : 0u) << q;
+            }
+            guard[lane] = (uint8_t)bits;
+            if (lane == 0) level = m;
         }
+        __syncthreads();
+        const float med = level;
+        const float inv = 1.0f / (med > 0.f ? med : 1.f);
+        const uint32_t gcol = (guard[(c0 + col) >> 2] >> (col & 3)) & 1u;  // of this lane's output column
         // x of tile row r -> input ring slot (r + 1) mod 8, zero outside the tile
         auto x_put = [&](int r, float pv) {
             const float v = (r >= 0 && r < H) ? __logf(1.0f + pv * inv) : 0.f;
@@ -764,26 +848,63 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
         csum = 0.f;
         __syncthreads();
 
-        half8 Fa[3], Fb[3];  // layer-1 operands of rows 2j - 3, 2j - 2, read by the previous step
-#pragma unroll
-        for (int dv = 0; dv < 3; ++dv) Fa[dv] = Fb[dv] = zero8;
-
-        auto step = [&](const int j, auto slot_tag) {
+        // The stages of a step.  BODY: steps 3 .. 30, where every stage has its rows.
+        // Rows of the input, layer 1 and the logits (mostly the vector ALUs and the LDS):
+        auto stage_rows = [&](const int j, auto slot_tag, auto body_tag) __attribute__((always_inline)) {
             constexpr int SL = decltype(slot_tag)::value;  // (j + 1) mod 4
+            constexpr bool BODY = decltype(body_tag)::value;
             float &xs_slot = SL == 0 ? xr0 : SL == 1 ? xr1 : SL == 2 ? xr2 : xr3;
-            // (a) input row 2j + 5 + xh; row 2j + 13 + xh is fetched for step j + 4, and row
-            //     2j + 2 + xh of the next tile for its column sums (added one step later).
-            //     Both loads are issued at every step (rows clamped into the tile, values
-            //     past its end unused), so the loads in flight are the same on every path.
+            // layer 1 for rows R, R + 1, R = 2j + 2 (input rows R - 1 .. R + 2); row 64 is zero
+            const int R = 2 * j + 2;
+            const int r3 = 2 * j - 6;  // logits of rows r3 (lanes 0-31) and r3 + 1 (lanes 32-63)
+            const int r = r3 + half;
+            u32x4 bx;
+            float uv[3][3];
+            if (BODY || R < H) {
+                const uint32_t *xr = xl + (((R + 2 * half) & (RX - 1)) >> 1);
+#pragma unroll
+                for (int dv = 0; dv < 4; ++dv) bx[dv] = xr[dv * (XPITCH / 2)];
+            }
+            if (BODY || (r3 >= 0 && r3 < H)) {
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    const float *row = ur + ((r + u - 1) & (RX - 1)) * UROW;
+#pragma unroll
+                    for (int v = 0; v < 3; ++v) uv[u][v] = row[9 * v + 3 * u + v];
+                }
+            }
+            float16v D1;
+            if (BODY || R < H) {
+                bx[3] = (bx[3] & bias_and) | bias_or;
+                D1 = __builtin_amdgcn_mfma_f32_32x32x16_f16(A1, __builtin_bit_cast(half8, bx), zero16, 0, 0, 0);
+            }
+            if (BODY || (r3 >= 0 && r3 < H)) {
+                float z = b3;
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    const int rr = r + u - 1;
+                    float zu = 0.f;
+#pragma unroll
+                    for (int v = 0; v < 3; ++v) zu += uv[u][v];
+                    z += ((BODY && u > 0) || (rr >= 0 && (BODY || rr < H))) ? zu : 0.f;  // BODY: rr -1 .. 56
+                }
+                const uint32_t gp = roff(r, c0 + col);
+                fb[gp] = (uint8_t)((z > thr_logit ? 1u : 0u) | gcol);
+                if constexpr (LOGITS) lb[gp] = z;
+            }
+            // input row 2j + 5 + xh; row 2j + 13 + xh is fetched for step j + 4, and row
+            // 2j + 2 + xh of the next tile for its column sums (added one step later).
+            // Both loads are issued at every step (rows clamped into the tile, values
+            // past its end unused), so the loads in flight are the same on every path.
             {
-                const int r = 2 * j + 5 + xh;
-                x_put(r, xs_slot);
-                xs_slot = tb[roff(r + 8 < H ? r + 8 : H - 1, xc)];
-                if (j >= 0 && j <= H / 2 - 1) csum += cnext;
+                const int rx = 2 * j + 5 + xh;
+                x_put(rx, xs_slot);
+                xs_slot = tb[roff(rx + 8 < H ? rx + 8 : H - 1, xc)];
+                if (BODY || (j >= 0 && j <= H / 2 - 1)) csum += cnext;
                 const int rc = 2 * j + 2 + xh;
                 const float cn = tn[roff(rc < H ? (rc > 0 ? rc : 0) : H - 1, xc)];
-                cnext = (j <= H / 2 - 2 && has_next) ? cn : 0.f;
-                if (j == H / 2 && has_next) {
+                cnext = ((BODY || j <= H / 2 - 2) && has_next) ? cn : 0.f;
+                if (!BODY && j == H / 2 && has_next) {
                     p0 = xh ? tn[xc] : 0.f;
                     p1 = tn[roff(1 + xh, xc)];
                     p2 = tn[roff(3 + xh, xc)];
@@ -792,16 +913,7 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
                     p5 = tn[roff(9 + xh, xc)];
                 }
             }
-            // (b) layer 1 for rows R, R + 1, R = 2j + 2 (input rows R - 1 .. R + 2); row 64 is zero
-            const int R = 2 * j + 2;
-            if (R < H) {
-                const uint32_t *xr = xl + (((R + 2 * half) & (RX - 1)) >> 1);
-                u32x4 bx;
-#pragma unroll
-                for (int dv = 0; dv < 4; ++dv) bx[dv] = xr[dv * (XPITCH / 2)];
-                bx[3] = (bx[3] & bias_and) | bias_or;
-                const float16v D =
-                    __builtin_amdgcn_mfma_f32_32x32x16_f16(A1, __builtin_bit_cast(half8, bx), zero16, 0, 0, 0);
+            if (BODY || R < H) {
 #pragma unroll
                 for (int sl = 0; sl < 2; ++sl) {
                     char *row = a1base + ((R + sl) & (RX - 1)) * AROW;
@@ -809,8 +921,8 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
                     for (int g = 0; g < 2; ++g) {
                         const int j0 = 8 * sl + 4 * g;
                         uint2 v;
-                        v.x = relu_h2(D[j0 + 0], D[j0 + 1]);
-                        v.y = relu_h2(D[j0 + 2], D[j0 + 3]);
+                        v.x = relu_h2(D1[j0 + 0], D1[j0 + 1]);
+                        v.y = relu_h2(D1[j0 + 2], D1[j0 + 3]);
                         *reinterpret_cast<uint2 *>(row + (g ? a1w1 : a1w0)) = v;
                     }
                 }
@@ -819,74 +931,22 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
                 *reinterpret_cast<uint2 *>(row + a1w0) = make_uint2(0u, 0u);
                 *reinterpret_cast<uint2 *>(row + a1w1) = make_uint2(0u, 0u);
             }
-            // (c) layer 2 and the tap sums for rows r2, r2 + 1, r2 = 2j - 2 (layer-1 rows r2 - 1 .. r2 + 2)
-            if (j >= 0 && j <= H / 2) {
-                half8 Fc[3], Fd[3];  // layer-1 rows 2j - 1, 2j
-                const char *fc = a1base + ((2 * j - 1) & (RX - 1)) * AROW;
-                const char *fd = a1base + ((2 * j) & (RX - 1)) * AROW;
-#pragma unroll
-                for (int dv = 0; dv < 3; ++dv) {
-                    Fc[dv] = *reinterpret_cast<const half8 *>(fc + a1rd[dv]);
-                    Fd[dv] = *reinterpret_cast<const half8 *>(fd + a1rd[dv]);
-                }
-                if (j >= 1) {
-                    const int r2 = 2 * j - 2;
-                    float16v D = bias2;
-#pragma unroll
-                    for (int dv = 0; dv < 3; ++dv) D = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[0][dv], Fa[dv], D, 0, 0, 0);
-#pragma unroll
-                    for (int dv = 0; dv < 3; ++dv) D = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[1][dv], Fb[dv], D, 0, 0, 0);
-#pragma unroll
-                    for (int dv = 0; dv < 3; ++dv) D = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[2][dv], Fc[dv], D, 0, 0, 0);
-#pragma unroll
-                    for (int dv = 0; dv < 3; ++dv) D = __builtin_amdgcn_mfma_f32_32x32x16_f16(A2[3][dv], Fd[dv], D, 0, 0, 0);
-#pragma unroll
-                    for (int sl = 0; sl < 2; ++sl) {
-                        u32x4 bu;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) bu[q] = relu_h2(D[8 * sl + 2 * q], D[8 * sl + 2 * q + 1]);
-                        const float16v U =
-                            __builtin_amdgcn_mfma_f32_32x32x16_f16(A3, __builtin_bit_cast(half8, bu), zero16, 0, 0, 0);
-                        float *dst = uw + ((r2 + sl) & (RX - 1)) * UROW;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) dst[4 * half + q] = U[q];
-                        if (half == 0) dst[8] = U[4];
-                    }
-                }
-#pragma unroll
-                for (int dv = 0; dv < 3; ++dv) {
-                    Fa[dv] = Fc[dv];
-                    Fb[dv] = Fd[dv];
-                }
-            }
-            // (d) logits of rows 2j - 6 (lanes 0-31) and 2j - 5 (lanes 32-63)
-            const int r3 = 2 * j - 6;
-            if (r3 >= 0 && r3 < H) {
-                const int r = r3 + half;
-                float z = b3;
-#pragma unroll
-                for (int u = 0; u < 3; ++u) {
-                    const int rr = r + u - 1;
-                    const float *row = ur + (rr & (RX - 1)) * UROW;
-                    float zu = 0.f;
-#pragma unroll
-                    for (int v = 0; v < 3; ++v) zu += row[9 * v + 3 * u + v];
-                    z += (rr >= 0 && rr < H) ? zu : 0.f;
-                }
-                const uint32_t gp = roff(r, c0 + col);
-                fb[gp] = (uint8_t)((z > thr_logit ? 1u : 0u) | gcol);
-                if (lb) lb[gp] = z;
-            }
-            __syncthreads();
         };
         // steps -1 .. 34, four at a time: 2j mod 8 is fixed within each group
-        for (int i = 0; i < (H / 2 + 4) / 4; ++i) {
-            const int jb = 4 * i - 1;
-            step(jb, std::integral_constant<int, 0>{});
-            step(jb + 1, std::integral_constant<int, 1>{});
-            step(jb + 2, std::integral_constant<int, 2>{});
-            step(jb + 3, std::integral_constant<int, 3>{});
-        }
+        auto steps = [&](const int jb, auto body_tag) __attribute__((always_inline)) {
+            stage_rows(jb, std::integral_constant<int, 0>{}, body_tag);
+            __syncthreads();
+            stage_rows(jb + 1, std::integral_constant<int, 1>{}, body_tag);
+            __syncthreads();
+            stage_rows(jb + 2, std::integral_constant<int, 2>{}, body_tag);
+            __syncthreads();
+            stage_rows(jb + 3, std::integral_constant<int, 3>{}, body_tag);
+            __syncthreads();
+        };
+        steps(-1, std::false_type{});
+#pragma unroll 1
+        for (int i = 1; i < H / 8; ++i) steps(4 * i - 1, std::true_type{});
+        steps(H / 2 - 1, std::false_type{});
     }
 }
 
@@ -950,12 +1010,16 @@ hipError_t launch_cnn_infer(const float *params, const void *power, bool f16, in
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         cus = 256;
     const int grid = std::max(1, std::min(n_tiles, cus));
-    if (f16)
-        hipLaunchKernelGGL(cnn_infer_kernel<_Float16>, dim3(grid), dim3(IWG), 0, st, params,
-                           static_cast<const _Float16 *>(power), T, C, n_tiles, thr_logit, guard_m, flags, logits);
-    else
-        hipLaunchKernelGGL(cnn_infer_kernel<float>, dim3(grid), dim3(IWG), 0, st, params,
-                           static_cast<const float *>(power), T, C, n_tiles, thr_logit, guard_m, flags, logits);
+    auto launch = [&](auto kernel, auto *p) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(IWG), 0, st, params, p, T, C, n_tiles, thr_logit, guard_m, flags,
+                           logits);
+    };
+    const _Float16 *p16 = static_cast<const _Float16 *>(power);
+    const float *p32 = static_cast<const float *>(power);
+    if (f16 && logits) launch(cnn_infer_kernel<_Float16, true>, p16);
+    else if (f16) launch(cnn_infer_kernel<_Float16, false>, p16);
+    else if (logits) launch(cnn_infer_kernel<float, true>, p32);
+    else launch(cnn_infer_kernel<float, false>, p32);
     return hipGetLastError();
 }
 
