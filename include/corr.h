@@ -184,8 +184,9 @@ int32_t corr_plan_x_splits(const corr_plan_t *plan);
  * (as a profiler lists it: "fengine4_kernel<log2 M, mode>" for the four-step
  * one, "fengine_kernel<...>" for the LDS-radix one; mode 0 FP32, 1 int8, 2
  * e4m3, plus 4 in table mode), for a call without power cells (with them the
- * four-step kernel's mode adds 4 for FP32 and 8 for FP16 cells).  The string
- * is valid until the calling thread's next call; "" for a NULL plan. */
+ * four-step kernel's mode adds 4 for FP32 and 8 for FP16 cells, the LDS-radix
+ * kernel's 8, and 512-channel FP32 spectra come from the LDS-radix kernel).  The
+ * string is valid until the calling thread's next call; "" for a NULL plan. */
 const char *corr_plan_fengine_kernel(const corr_plan_t *plan);
 
 /* Attach caller-owned device workspace (>= workspace_bytes, 256-byte

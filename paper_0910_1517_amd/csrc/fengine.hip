@@ -71,6 +71,13 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 }
 __device__ __forceinline__ float2 mul_mi(float2 a) { return make_float2(a.y, -a.x); }  // * (-i)
 
+// The product of the output stage, with its roundings written out: left to the
+// compiler, which of the two products of the imaginary part is rounded before the
+// addition depends on the code around it, and with it codes near a boundary.
+__device__ __forceinline__ float2 cmul_out(float2 a, float2 b) {
+    return make_float2(fmaf(a.x, b.x, -(a.y * b.y)), fmaf(a.y, b.x, a.x * b.y));
+}
+
 constexpr float kRsqrt2 = 0.70710678118654752440f;
 
 // 4-point DFT, forward sign, outputs in natural order.
@@ -265,6 +272,7 @@ fengine_kernel(FLaunch a) {
     using C = FCfg<LOGM>;
     constexpr int BM = MODE & 3;          // 0 FP32, 1 INT8, 2 FP8, 3 calibration
     constexpr bool PL = (MODE & 4) != 0;  // phase from the 1440-step table
+    constexpr bool PW = (MODE & 8) != 0;  // with power cells (FP32 or FP16, uniform)
     constexpr int M = C::M, N = C::N, L = C::L, FPAR = C::FPAR;
     const int sps = BM == 3 ? 16 : a.sps;  // spectra per transform slot (a power of two, whole chunks)
     const int SPB = sps * FPAR;            // spectra per workgroup
@@ -433,7 +441,17 @@ fengine_kernel(FLaunch a) {
         // next window only after them, so that waiting for a table load never
         // waits for the window (loads complete in issue order), and the window
         // is not held in registers through the transform
-        float2 wv[8], ev[8];
+        float2 wv[8], ev[8], f1[8];
+        float pv[8];
+        // FP32 chunk of channel j, complete after the odd spectrum.  LATE: chunks and cells
+        // are stored after all the channels' arithmetic.  (FP32 with the phase table at
+        // 8192 channels keeps a branch at each, with cells or without: 64 x 8192 x 512
+        // 1455 us, 1505 late.  Elsewhere late is as fast or faster.)
+        constexpr bool LATE = !(BM == 0 && PL && LOGM == 13);
+        auto store32 = [&](int j) __attribute__((always_inline)) {
+            float4 *dst = reinterpret_cast<float4 *>(a.spec) + obase + (int64_t)j * L * a.S;
+            *dst = make_float4(f0[j].x, f0[j].y, f1[j].x, f1[j].y);
+        };
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             wv[j] = wn[tt + L * j];
@@ -450,37 +468,38 @@ fengine_kernel(FLaunch a) {
             const float2 w = wv[j];
             // 2 X = (a + b) - i w (a - b)
             float2 X;
-            X.x = sm.x + (w.x * df.y + w.y * df.x);
-            X.y = sm.y - (w.x * df.x - w.y * df.y);
+            X.x = sm.x + fmaf(w.x, df.y, w.y * df.x);
+            X.y = sm.y - fmaf(w.x, df.x, -(w.y * df.y));
             if constexpr (BM == 3) {
                 pacc[j] += X.x * X.x + X.y * X.y;
             } else {
-                if (a.power && active)  // |X|^2 = |2X|^2 / 4 (the phase rotation keeps it)
-                    put_power(a, ((int64_t)s * a.T + m) * M + tt + L * j, 0.25f * (X.x * X.x + X.y * X.y));
+                if constexpr (PW || !LATE) {  // |X|^2 = |2X|^2 / 4 (the phase rotation keeps it)
+                    pv[j] = 0.25f * fmaf(X.x, X.x, X.y * X.y);
+                    if constexpr (!LATE)
+                        if (a.power && active) put_power(a, ((int64_t)s * a.T + m) * M + tt + L * j, pv[j]);
+                }
                 // the value; for int8 the value plus 128, formed inside its last products
                 float2 Y;
                 if constexpr (PL) {  // table entry nearest the channel's phase; ramp = 1/2 (x 1/scale)
                     const float2 e = ev[j];
-                    const float2 u = make_float2(X.x * e.x - X.y * e.y, X.x * e.y + X.y * e.x);
+                    const float2 u = cmul_out(X, e);
                     if constexpr (BM == 1)
                         Y = make_float2(fmaf(ramp[j].x, u.x, 128.0f), fmaf(ramp[j].x, u.y, 128.0f));
                     else
                         Y = make_float2(ramp[j].x * u.x, ramp[j].x * u.y);
                 } else if constexpr (BM == 1) {
-                    const float2 t = cmul(X, ramp[j]);
+                    const float2 t = cmul_out(X, ramp[j]);
                     Y = make_float2(fmaf(t.x, rot.x, fmaf(-t.y, rot.y, 128.0f)),
                                     fmaf(t.x, rot.y, fmaf(t.y, rot.x, 128.0f)));
                 } else {
-                    Y = cmul(cmul(X, ramp[j]), rot);
+                    const float2 t = cmul_out(X, ramp[j]);
+                    Y = make_float2(fmaf(t.x, rot.x, -(t.y * rot.y)), fmaf(t.x, rot.y, t.y * rot.x));
                 }
                 if constexpr (BM == 0) {
-                    if (r & 1) {
-                        if (active) {
-                            float4 *dst = reinterpret_cast<float4 *>(a.spec) + obase + (int64_t)j * L * a.S;
-                            *dst = make_float4(f0[j].x, f0[j].y, Y.x, Y.y);
-                        }
-                    } else {
-                        f0[j] = Y;
+                    f1[j] = Y;
+                    if constexpr (!LATE) {
+                        if ((r & 1) == 0) f0[j] = Y;
+                        else if (active) store32(j);
                     }
                 } else {
                     // insert the byte of spectrum r into byte r mod 4 of the chunk's
@@ -496,11 +515,35 @@ fengine_kernel(FLaunch a) {
                         q = __builtin_amdgcn_perm(w, q, bsel);
                         h = __builtin_amdgcn_perm(w, h, bsel + (1u << (8 * (r & 3))));
                     }
-                    if (NH == 1 && (r & 7) == 3) {
-                        q0[j] = q1[j];
-                        h0[j] = h1[j];
-                    }
                 }
+            }
+        }
+        if constexpr ((BM == 1 || BM == 2) && NH == 1) {
+            if ((r & 7) == 3) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    q0[j] = q1[j];
+                    h0[j] = h1[j];
+                }
+            }
+        }
+        // the stores, after the channels' arithmetic: a branch at each channel kept
+        // the compiler from overlapping one's LDS reads with another's arithmetic, and
+        // cost a tenth of the vector instructions in addresses.  64 signals of 2^24
+        // samples: int8 at 4096 channels 1490 -> 1443 us, with FP16 cells 1780 -> 1636,
+        // FP32 1950 -> 1871; at 512 with FP16 cells int8 1475 -> 1315
+        if constexpr (PW && LATE) {
+            if (active)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) put_power(a, ((int64_t)s * a.T + m) * M + tt + L * j, pv[j]);
+        }
+        if constexpr (BM == 0 && LATE) {
+            if ((r & 1) == 0) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) f0[j] = f1[j];
+            } else if (active) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) store32(j);
             }
         }
     }
@@ -536,14 +579,19 @@ hipError_t launch_one(int mode, FLaunch a, hipStream_t st) {
     const int spb = a.sps * C::FPAR;
     const int nblk = (a.T + spb - 1) / spb;
     const dim3 grid(a.S * nblk), block(C::WG);
-    switch (mode) {
-    case 0: hipLaunchKernelGGL((fengine_kernel<LOGM, 0>), grid, block, 0, st, a); break;
-    case 1: hipLaunchKernelGGL((fengine_kernel<LOGM, 1>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((fengine_kernel<LOGM, 2>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((fengine_kernel<LOGM, 3>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((fengine_kernel<LOGM, 4>), grid, block, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((fengine_kernel<LOGM, 5>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((fengine_kernel<LOGM, 6>), grid, block, 0, st, a); break;
+    // power cells are a template choice, as in the four-step kernel; what that kernel
+    // serves (use_fengine4) is not built here
+    switch (mode + (mode != 3 && a.power ? 8 : 0)) {
+#define F_CASE(m)                                                                                              \
+    case m:                                                                                                    \
+        if constexpr (!use_fengine4(LOGM, (m) & 7, ((m) & 8) != 0))                                            \
+            hipLaunchKernelGGL((fengine_kernel<LOGM, m>), grid, block, 0, st, a);                              \
+        else                                                                                                   \
+            return hipErrorInvalidValue;                                                                       \
+        break;
+    F_CASE(0) F_CASE(1) F_CASE(2) F_CASE(3) F_CASE(4) F_CASE(5) F_CASE(6)
+    F_CASE(8) F_CASE(9) F_CASE(10) F_CASE(12) F_CASE(13) F_CASE(14)
+#undef F_CASE
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

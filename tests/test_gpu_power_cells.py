@@ -60,3 +60,34 @@ def test_512_channel_fp32_spectra_with_and_without_cells(S, T):
     # each kernel's error is near 1.5e-7 of the spectra's rms (FP32 sums of 10 stages);
     # the largest of some 1e6 differences stays within 9 times the two together
     assert (a - b).abs().max() <= 2e-6 * (a ** 2).mean().sqrt()
+
+
+@pytest.mark.parametrize("lut", [0, 1])
+@pytest.mark.parametrize("prec", [corr.FP32, corr.INT8, corr.FP8_E4M3])
+@pytest.mark.parametrize("N", [512, 1024, 4096, 8192, 16384])
+def test_spectra_do_not_depend_on_the_cells(N, prec, lut):
+    """Launches with and without cells are separate kernels; their spectra are the
+    same bytes (but for 512-channel FP32 spectra without the table, above), and the
+    FP16 cells are the FP32 ones rounded."""
+    import torch
+    S, T = 3, 96
+    g = geom_dev(synth.make_geometry(2, seed=N).subset(np.arange(S)))
+    rs = row_stride_for(N, T, 16)
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.randint(-127, 128, (S, rs), generator=gen, device="cuda", dtype=torch.int8)
+    scale = torch.full((S, N // 2), 30.0, device="cuda") if prec != corr.FP32 else None
+
+    def run(cells, half):
+        plan = corr.Plan(S, N, T, precision=prec, phase_lut=lut, power_fp16=half)
+        spec = plan.alloc("spectra", zero=False).fill_(0xA5)
+        power = plan.alloc("power", zero=False) if cells else None
+        plan.fengine(x, g, spec, scale, power=power, row_stride=rs, spectrum0=1)
+        return spec, power
+
+    plain, _ = run(False, 0)
+    full, p32 = run(True, 0)
+    again, p16 = run(True, 1)
+    assert torch.equal(full, again)
+    if not (N == 1024 and prec == corr.FP32 and lut == 0):
+        assert torch.equal(plain, full)
+    assert torch.equal(p16, (p32 * 2.0 ** -(2 * (N.bit_length() - 1))).half())
