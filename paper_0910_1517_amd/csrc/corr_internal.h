@@ -118,9 +118,9 @@ __device__ __forceinline__ void put_power(const FLaunch &a, int64_t i, float p) 
 // measured, 64 signals of 2^24 samples, us per call:
 //   log2 M                      8     9     10    11    12
 //   int8 output: four-step     765   876   884   901
-//                LDS-radix    1077  1094  1272  1308  1490
-//   FP32 output: four-step    1507  1316  1303  1282
-//                LDS-radix    1671  1703  1817  1879  1949
+//                LDS-radix    1051  1090  1261  1287  1451
+//   FP32 output: four-step    1503  1318  1303  1282
+//                LDS-radix    1647  1688  1799  1847  1871
 // At 9 the four-step kernel rounds differently from the LDS-radix one, which has
 // always served that length: FP32 spectra are a little nearer to 64 bits (1.385e-7
 // against 1.412e-7; noise of one bit to full scale and tones 2 to 8% less), but
