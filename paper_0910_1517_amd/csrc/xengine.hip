@@ -780,8 +780,8 @@ __device__ __forceinline__ void transpose4(const uint32_t (&w)[4], uint32_t (&ou
 
 __global__ void __launch_bounds__(256) xpack8_kernel(const uint8_t *__restrict__ in, uint4 *__restrict__ out, int S,
                                                      int64_t T, int lgC) {
-    const int64_t idx = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);  // over [T/8][C/8]
-    const int s = blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int64_t idx = (int64_t)blockIdx.x * 64 + threadIdx.x;  // over [T/8][C/8]
+    const int s = blockIdx.y * 4 + threadIdx.y;
     if (s >= S) return;
     const int64_t g = idx >> (lgC - 3), kb = idx & ((1 << (lgC - 3)) - 1);
     const uint4 *src = reinterpret_cast<const uint4 *>(in + ((((int64_t)s * T + 8 * g) << lgC) + 8 * kb) * 2);
@@ -807,8 +807,8 @@ __global__ void __launch_bounds__(256) xpack8_kernel(const uint8_t *__restrict__
 // FP32: a thread takes one channel of 2 spectra, one chunk; 8 lanes fill a line.
 __global__ void __launch_bounds__(256) xpack32_kernel(const float2 *__restrict__ in, float4 *__restrict__ out, int S,
                                                       int64_t T, int lgC) {
-    const int64_t idx = (int64_t)blockIdx.x * 64 + (threadIdx.x & 63);  // over [T/2][C]
-    const int s = blockIdx.y * 4 + (threadIdx.x >> 6);
+    const int64_t idx = (int64_t)blockIdx.x * 64 + threadIdx.x;  // over [T/2][C]
+    const int s = blockIdx.y * 4 + threadIdx.y;
     if (s >= S) return;
     const int64_t g = idx >> lgC, k = idx & ((1 << lgC) - 1);
     const float2 *src = in + (((int64_t)s * T + 2 * g) << lgC) + k;
@@ -952,13 +952,16 @@ hipError_t launch_xengine_batch(const XBatchArgs &a, hipStream_t st) {
 }
 
 hipError_t launch_xpack(int precision, const void *in, void *spec, int S, int C, int T, hipStream_t st) {
-    // T is a multiple of 32 and C a power of two >= 256, so the waves are whole
+    // T is a multiple of 32 and C a power of two >= 256, so the waves are whole.  The
+    // signals are the y extent of grid and workgroup: a launch has fewer than 2^32
+    // threads in x, here T C / 2 at most, whatever S is (FP32 spectra of 64 GiB a signal).
     const unsigned ny = (unsigned)((S + 3) / 4);
+    const dim3 block(64, (unsigned)(S < 4 ? S : 4));
     if (precision == CORR_FP32)
-        hipLaunchKernelGGL(xpack32_kernel, dim3((unsigned)((int64_t)(T / 2) * C / 64), ny), dim3(256), 0, st,
+        hipLaunchKernelGGL(xpack32_kernel, dim3((unsigned)((int64_t)(T / 2) * C / 64), ny), block, 0, st,
                            (const float2 *)in, (float4 *)spec, S, (int64_t)T, log2_of(C));
     else
-        hipLaunchKernelGGL(xpack8_kernel, dim3((unsigned)((int64_t)(T / 8) * (C / 8) / 64), ny), dim3(256), 0, st,
+        hipLaunchKernelGGL(xpack8_kernel, dim3((unsigned)((int64_t)(T / 8) * (C / 8) / 64), ny), block, 0, st,
                            (const uint8_t *)in, (uint4 *)spec, S, (int64_t)T, log2_of(C));
     return hipGetLastError();
 }
