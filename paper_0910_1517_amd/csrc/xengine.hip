@@ -427,9 +427,14 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
 //
 // Values of 2^-100 and more in magnitude (and zeros) split exactly.  A value
 // that is infinite or NaN, or within half a BF16 step of the largest FP32
-// number, leaves a NaN in every sum it takes part in; a block that ends with
-// a sum that is not finite is done again on the FP32 instructions, so such data
-// give what they always gave.
+// number, leaves a NaN in every sum it takes part in; a block with a sum that is
+// not finite is done on the FP32 instructions instead, all its 8 channels (so a bad
+// cell moves the last bits of the other seven): the bad pairs come out as those
+// instructions give them.  A dead antenna, NaN throughout, shows before the first
+// step and costs what it cost when every block ran on the FP32 instructions (64 x
+// 512 x 16384: 1510 us, 1490 then; two gates 2950 and 3540); found only at the end of
+// a block, by a fallback that spilled, it had cost 3600 us.  A bad cell elsewhere
+// costs its own block what both passes take, at most.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
@@ -453,6 +458,39 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t (&p)[3]) {
 
 constexpr int kSplitChunks = 8;  // chunks of 2 spectra per K-step
 
+// A value that is the same in every lane, into scalar registers (the arguments of a
+// function call and the results of divisions come in vector registers).
+template <typename T>
+__device__ __forceinline__ T uniform(T v) {
+    union {
+        T v;
+        int w[sizeof(T) / 4];
+    } u;
+    u.v = v;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(T) / 4); ++i) u.w[i] = __builtin_amdgcn_readfirstlane(u.w[i]);
+    return u.v;
+}
+
+// The block on the FP32 instructions, a function of its own: inlined behind the
+// block below, whose registers are all in use, its prefetch went through scratch
+// memory with a wait for every load, and the registers of both went there too (49 to
+// 62 a lane; two gates at 64 x 512 x 16384 2260 us so, 1930 as a call).  Pointers have
+// their address space: generic ones would make every access a flat one, which waits
+// for LDS and memory alike.
+#define GLOBAL_ __attribute__((address_space(1)))
+#define LDS_ __attribute__((address_space(3)))
+template <int NT, bool GATED, bool MASKED>
+__device__ __attribute__((noinline)) void xengine_block_fp32(const GLOBAL_ uint8_t *spec, GLOBAL_ float *out, int S,
+                                                             int C, int T, int splits, int kb, int sp,
+                                                             LDS_ uint8_t *lds, const GLOBAL_ uint8_t *gate, int bin,
+                                                             const GLOBAL_ uint32_t *keep) {
+    xengine_block<NT, CORR_FP32, float, GATED, MASKED>(
+        (const uint8_t *)uniform(spec), (float *)uniform(out), uniform(S), uniform(C), uniform(T), uniform(splits),
+        uniform(kb), uniform(sp), (uint8_t *)uniform(lds), (const uint8_t *)uniform(gate), uniform(bin),
+        (const uint32_t *)uniform(keep));
+}
+
 // The block of xengine_block, for FP32 spectra.  A K-step is 16 spectra: lanes
 // 0-31 take its first four chunks of their signal, lanes 32-63 the other four
 // (8 spectra each, the K slots of a lane).  The chunks go from global memory
@@ -473,7 +511,7 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
     static_assert(2 * kSplitChunks * blk <= x_lds_bytes<NT>(), "both buffers fit");
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = kXWaves * kb + wv;
     const int lane = threadIdx.x & 63, row = lane & 31, lg = lane >> 5;
-    const int steps = T / (2 * kSplitChunks) / splits;
+    const int steps = uniform(T / (2 * kSplitChunks) / splits);  // (a division leaves it in a vector register)
     const int64_t P = (int64_t)S * (S + 1) / 2;
     if (steps < 1) return;
 
@@ -489,11 +527,13 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
         if (cp) {
 #pragma unroll
             for (int j = 0; j < kSplitChunks; ++j)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + j * gstride),
-                                                 (__attribute__((address_space(3))) void *)(l + j * blk), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((const GLOBAL_ void *)(g + j * gstride), (LDS_ void *)(l + j * blk), 16, 0,
+                                                 0);
         }
     };
-    // keep bits of this lane's 8 spectra of a step, per row tile
+    // keep bits of this lane's 8 spectra of a step, per row tile (shifted at once,
+    // which waits for the chunks in flight: 1260 us at 64 x 512 x 16384, 1295 with the
+    // shift a phase later)
     uint32_t kb8[NT];
     const uint32_t *kw = nullptr;
     uint32_t koff[NT];
@@ -602,10 +642,34 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     };
+    // Data that are not finite are done on the FP32 instructions (below); most such data,
+    // an antenna that is NaN throughout, show in the first chunk, which each thread
+    // looks at where it has put it, before a step is lost on them.
+    __shared__ __attribute__((aligned(16))) uint32_t spoilt[2][kXWaves];
+    auto not_finite = [](float x) __attribute__((always_inline)) { return __builtin_amdgcn_classf(x, 0x207); };
     stage(0, 0);
     load_keep(0);
     load_gate(0);
-    arrived();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    bool bad = false;
+    if (cp) {
+        v4u x = *reinterpret_cast<const v4u *>(lds + i * 16);
+        if constexpr (MASKED) {
+            const int64_t s_ = (int64_t)sp * steps;
+            const uint32_t k = (kw + (s_ >> 1) * S * 8)[si * 8 + ((i & 7) ^ (si & 7))] >> (16 * (s_ & 1));
+            const uint32_t m0 = 0u - (k & 1u), m1 = 0u - (k >> 1 & 1u);
+            x &= v4u{m0, m0, m1, m1};
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bad |= not_finite(__uint_as_float(x[q]));
+    }
+    spoilt[0][wv] = __any(bad);
+    __syncthreads();
+    auto told = [&](int turn) __attribute__((always_inline)) {  // by any wave
+        const v4u *w = reinterpret_cast<const v4u *>(spoilt[turn]), c = w[0] | w[1];
+        return __builtin_amdgcn_readfirstlane(c[0] | c[1] | c[2] | c[3]) != 0;
+    };
+    bool redo = told(0);
     if constexpr (NT == 2) {
         // The parts of row tile 0 are made a phase ahead of their use, and those of
         // tile 1 during the products of tile 0, so that vector and matrix
@@ -620,39 +684,49 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
         stage(clamped(1), 1);
         load_keep(clamped(1));
         split(0, 0, k8[0]);
+        // What is not finite later shows in the sums: after every kSpan steps each wave
+        // looks at one register of the tiles on the diagonal (a bad signal spoils its
+        // whole column there) and tells the others, who read it a span later and all
+        // leave.  (Two sets of words in turn: none is written where a wave may still read.)
+        constexpr int kSpan = 16;
+        for (int st = 0, end, turn = 0; st < steps && !redo; turn ^= 1) {
+            end = min(steps, st + kSpan);
 #pragma unroll 1
-        for (int st = 0; st < steps; ++st) {
-            __builtin_amdgcn_sched_barrier(0);
-            split(1, st, k8[1]);
-            tiles(integral_constant<int, 0>{}, integral_constant<int, 3>{});
-            X_MIX(18, 6)
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (MASKED) {
-                k8[0] = kb8[0];
-                k8[1] = kb8[1];
+            for (; st < end; ++st) {
+                __builtin_amdgcn_sched_barrier(0);
+                split(1, st, k8[1]);
+                tiles(integral_constant<int, 0>{}, integral_constant<int, 3>{});
+                X_MIX(18, 6)
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (MASKED) {
+                    k8[0] = kb8[0];
+                    k8[1] = kb8[1];
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                stage(clamped(st + 2), st & 1);
+                load_keep(clamped(st + 2));
+                __builtin_amdgcn_sched_barrier(0);
+                tiles(integral_constant<int, 4>{}, integral_constant<int, 1>{}, integral_constant<int, 5>{});
+                X_MIX(24, 2)
+                __builtin_amdgcn_sched_barrier(0);
+                // step st + 1's chunks: all but the loads issued since (8, and the keep words;
+                // a wave without a signal of its own waits for nothing)
+                if constexpr (MASKED) asm volatile("s_waitcnt vmcnt(10)\n\ts_barrier" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+                split(0, st + 1, k8[0]);
+                tiles(integral_constant<int, 2>{}, integral_constant<int, 6>{});
+                X_MIX(18, 6)
+                __builtin_amdgcn_sched_barrier(0);
+                load_gate(clamped(st + 1));
             }
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            stage(clamped(st + 2), st & 1);
-            load_keep(clamped(st + 2));
-            __builtin_amdgcn_sched_barrier(0);
-            tiles(integral_constant<int, 4>{}, integral_constant<int, 1>{}, integral_constant<int, 5>{});
-            X_MIX(24, 2)
-            __builtin_amdgcn_sched_barrier(0);
-            // step st + 1's chunks: all but the loads issued since (8, and the keep words;
-            // a wave without a signal of its own waits for nothing)
-            if constexpr (MASKED) asm volatile("s_waitcnt vmcnt(10)\n\ts_barrier" ::: "memory");
-            else asm volatile("s_waitcnt vmcnt(8)\n\ts_barrier" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            split(0, st + 1, k8[0]);
-            tiles(integral_constant<int, 2>{}, integral_constant<int, 6>{});
-            X_MIX(18, 6)
-            __builtin_amdgcn_sched_barrier(0);
-            load_gate(clamped(st + 1));
+            redo = told(turn);
+            spoilt[turn ^ 1][wv] = __any(not_finite(acc[0][0]) | not_finite(acc[2][0]));
         }
         arrived();
     } else {
 #pragma unroll 1
-        for (int st = 0; st < steps; ++st) {
+        for (int st = 0; st < steps && !redo; ++st) {
             k8[0] = MASKED ? kb8[0] : 0u;
             if (st + 1 < steps) {  // into the buffer that was last read a step ago
                 stage(st + 1, (st + 1) & 1);
@@ -670,8 +744,13 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
     for (int t = 0; t < NTILE; ++t)
 #pragma unroll
         for (int r = 0; r < 16; ++r) z = fmaf(acc[t][r], 0.f, z);
-    if (__syncthreads_or(z != z)) {
-        xengine_block<NT, CORR_FP32, float, GATED, MASKED>(spec, out, S, C, T, splits, kb, sp, lds, gate, bin, keep);
+    if (redo || __syncthreads_or(z != z)) {
+        if constexpr (NT == 2)
+            xengine_block_fp32<NT, GATED, MASKED>((const GLOBAL_ uint8_t *)spec, (GLOBAL_ float *)out, S, C, T, splits, kb,
+                                                  sp, (LDS_ uint8_t *)lds, (const GLOBAL_ uint8_t *)gate, bin,
+                                                  (const GLOBAL_ uint32_t *)keep);
+        else  // (the registers suffice; a call would take half of a compute unit's workgroups)
+            xengine_block<NT, CORR_FP32, float, GATED, MASKED>(spec, out, S, C, T, splits, kb, sp, lds, gate, bin, keep);
         return;
     }
     v16f accR[ntri(NT)], accM[NT * NT];
@@ -721,8 +800,8 @@ xengine_gated_kernel(const uint8_t *__restrict__ spec, const uint8_t *__restrict
     const int nkb = C / kXWaves;
     if (task >= nkb * splits) return;  // padding of the last group of 8 tasks
     if constexpr (PREC == CORR_FP32)
-        xengine_block_split<NT, true, false>(spec, acc + part * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds,
-                                             gate, part, nullptr);
+        xengine_block_split<NT, true, false>(spec, acc + uniform(part) * acc_elems, S, C, T, splits, uniform(task % nkb),
+                                             uniform(task / nkb), lds, gate, uniform(part), nullptr);
     else if constexpr (NB == 1)
         xengine_block<NT, PREC, ACC, true>(spec, acc + part * acc_elems, S, C, T, splits, task % nkb, task / nkb, lds,
                                            gate, part);
