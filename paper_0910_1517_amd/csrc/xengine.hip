@@ -993,16 +993,25 @@ hipError_t launch_xengine(int precision, const void *spec, const uint32_t *keep,
 hipError_t launch_xengine_gated(int precision, const void *spec, const uint8_t *gate, int n_bins, void *acc,
                                 int64_t acc_elems, int S, int C, int T, int splits, hipStream_t st) {
     const int tasks = (C / kXWaves) * splits;
-    // pairs of bins (545 us for two at 64 x 2048 x 8192 int8, 330 us a bin alone): not for
-    // three, whose second pair is half empty (1090 against 990 us)
-    const bool pair = precision != CORR_FP32 && n_bins > 1 && n_bins != 3;
+    // Pairs of bins where the staging they share is what bounds a launch: from two K-steps
+    // a split on (four signals, eight bins of 512 channels x 64 spectra: 28.6 us in pairs, 26.4
+    // single; of 2048 x 512, eight steps: 62 and 71).  The empty half of an odd number's last
+    // pair costs a workgroup: five bins of 4 x 2048 x 64 22.4 and 17.8 us, of 64 x 8192 x 256
+    // 571 and 564, three of 64 x 2048 x 8192 1090 and 990.  With one signal tile it still pays
+    // off for more than 20 signals (five bins of 32 x 2048 x 512: 14% faster in pairs; of 24
+    // signals 4%; of 20, 2% slower) or from nine bins of eight steps on (4 x 2048 x 512: 4%; of four steps 5% slower).
+    const bool two = S > 32;
+    const int steps = T / 32 / splits;  // of 8-bit codes
+    const bool odd = !two && n_bins > 3 && (S > 20 || (n_bins >= 9 && steps >= 8));
+    const bool pair = precision != CORR_FP32 && steps > 1 && (n_bins % 2 == 0 || odd) &&
+                      // (the rounding up included, a launch has fewer than 2^32 threads in x)
+                      (int64_t)(tasks + kXcds) * (n_bins + 1) * 64 * kXWaves < (int64_t)1 << 32;
     const int per = pair ? 2 * ((n_bins + 1) / 2) : n_bins;
     const dim3 grid((unsigned)((tasks + kXcds - 1) / kXcds * kXcds * per)), block(64 * kXWaves);
     const uint8_t *sp8 = (const uint8_t *)spec;
     auto go = [&](auto kernel, auto *a) {
         hipLaunchKernelGGL(kernel, grid, block, 0, st, sp8, gate, a, acc_elems, S, C, T, splits, n_bins);
     };
-    const bool two = S > 32;
     int32_t *ai = (int32_t *)acc;
     float *af = (float *)acc;
     switch (precision) {

@@ -27,7 +27,7 @@ def exact(Y, weight=None):
     y = torch.from_numpy(Y).cuda().permute(2, 0, 1, 3).double()  # [C][S][T][2]
     w = y if weight is None else y * torch.from_numpy(weight.astype(np.float64)).cuda()[:, None]
     r, q, rw, qw = y[..., 0], y[..., 1], w[..., 0], w[..., 1]
-    dot = lambda a, b: torch.stack([a[k] @ b[k].T.contiguous() for k in range(C)])
+    dot = lambda a, b: torch.bmm(a.contiguous(), b.transpose(1, 2).contiguous())
     j, i = np.tril_indices(Y.shape[0])
     re, im = dot(r, rw) + dot(q, qw), dot(q, rw) - dot(r, qw)  # V[i][j] = sum y_i conj(y_j)
     return torch.stack([re[:, i, j], im[:, i, j]], -1).float().cpu().numpy()
