@@ -11,8 +11,8 @@
 // has no scale estimate and passes unchanged.
 //
 // A block (up to 64 KiB) is loaded once into registers, 32 G samples a lane,
-// by one wave up to 8192 samples and by two, four or eight above, and never
-// re-read.  Its statistics are exact order statistics taken bit by bit: each
+// by one wave up to 8192 samples (out of place 4096) and by two, four or eight
+// above, and never re-read.  Its statistics are exact order statistics taken bit by bit: each
 // group of 32 samples of a lane is transposed into 8 words, one per bit (word
 // p holds bit p of the 32 samples), after which one instruction handles 32
 // samples.  The k-th smallest value is found from its top bit down: of the
@@ -339,33 +339,66 @@ __global__ __launch_bounds__(NW == 1 ? 256 : 64 * NW) void blank_kernel(
     const double sigma = over_6745((double)mad4 * 0.25);
     // bit q of group g of lane l of this wave: chunk, word and byte of the block
     const int l0 = NW == 1 ? 0 : wave * 64;
-    auto blank = [&](int l, int g, int q) {
-        const int pos = (l0 + l + TB * (2 * g + ((q >> 2) & 1))) * 16 + 4 * (q & 3) + (q >> 3);
-        orow[pos] = (int8_t)replacement(half_med2, sigma, trow[(p_blk + pos) & Lmask]);
+    auto place = [&](int e) {
+        const int l = e >> 8, g = (e >> 5) & 7, q = e & 31;
+        return (l0 + l + TB * (2 * g + ((q >> 2) & 1))) * 16 + 4 * (q & 3) + (q >> 3);
     };
+    auto value = [&](int pos) { return trow[(p_blk + pos) & Lmask]; };
+    auto put = [&](int pos, float z) { orow[pos] = (int8_t)replacement(half_med2, sigma, z); };
     if constexpr (NW > 1) __syncthreads();  // out of place: every wave's copy is on its way
     const int lane = threadIdx.x & 63;
-    if (total > kBlankQueue) {  // more outliers than the queue holds (small M): each lane its own
+    // Each wave queues its blanked samples (lane, group, bit), then replaces them with
+    // all its lanes: all groups at once, or, where there are more than the queue holds
+    // (strong interference, a small M), a group at a time, whose samples always fit.
+    // 64 x 2^22 samples out of place, two thirds of them blanked: 293 us in blocks of 4096,
+    // 349 of 16384; with each lane replacing its own in that case 827 and 729.
+    static_assert(G <= 8, "14 bits an entry");
+    static_assert(64 * 32 <= kBlankQueue, "a group fits");
+    uint16_t *queue = queue_lds + wave * kBlankQueue;
+    auto push = [&](uint16_t *next, int g) {
+        for (uint32_t w = bad[g]; w; w &= w - 1) *next++ = (uint16_t)(lane << 8 | g << 5 | __builtin_ctz(w));
+        return next;
+    };
+    auto wave_order = [] {  // the wave's own LDS order suffices
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto replace = [&](int n) {
+        wave_order();
+        int i = lane;
+        // many: four table values of a lane in flight (one at a time each waits out the
+        // memory latency, which the few waves of the larger blocks do not hide: 64 x 2^22
+        // samples in blocks of 16384, bursts on 30%: 281 us so, 219 now)
+        constexpr int F = 4;
+        for (; n - (i - lane) >= 64 * F; i += 64 * F) {
+            int pos[F];
+            float z[F];
 #pragma unroll
-        for (int g = 0; g < G; ++g)
-            for (uint32_t w = bad[g]; w; w &= w - 1) blank(lane, g, __builtin_ctz(w));
+            for (int f = 0; f < F; ++f) pos[f] = place(queue[i + 64 * f]);
+#pragma unroll
+            for (int f = 0; f < F; ++f) z[f] = value(pos[f]);
+#pragma unroll
+            for (int f = 0; f < F; ++f) put(pos[f], z[f]);
+        }
+        for (; i < n; i += 64) {
+            const int pos = place(queue[i]);
+            put(pos, value(pos));
+        }
+    };
+    if (total <= kBlankQueue) {
+        uint16_t *next = queue + (pre - mine);
+#pragma unroll
+        for (int g = 0; g < G; ++g) next = push(next, g);
+        replace(total);
         return;
     }
-    // each wave queues its blanked samples (lane, group, bit), then replaces them
-    // with all its lanes
-    static_assert(G <= 8, "14 bits an entry");
-    uint16_t *queue = queue_lds + wave * kBlankQueue;
-    uint16_t *next = queue + (pre - mine);
 #pragma unroll
-    for (int g = 0; g < G; ++g)
-        for (uint32_t w = bad[g]; w; w &= w - 1) *next++ = (uint16_t)(lane << 8 | g << 5 | __builtin_ctz(w));
-    // the wave's own LDS order suffices
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    for (int i = lane; i < total; i += 64) {
-        const int e = queue[i];
-        blank(e >> 8, (e >> 5) & 7, e & 31);
+    for (int g = 0; g < G; ++g) {
+        const uint32_t own = (uint32_t)__builtin_popcount(bad[g]), upto = wave_prefix(own);
+        push(queue + (upto - own), g);
+        replace(__builtin_amdgcn_readlane((int)upto, 63));
+        wave_order();
     }
 }
 
@@ -445,12 +478,13 @@ corr_status corr_blank_voltages(const int8_t *d_x, int64_t row_stride, int32_t S
     // registers of a SIMD, above that groups of waves, whose sums meet in LDS.  us in
     // place at 64 x 2^24 samples, blocks of 16384: <8, 1> 444, <4, 2> 272; of 12288: <6, 1>
     // 295, <4, 2> 420; of 20000: <6, 2> 324, <4, 4> 432; out of place of 65536 early 538,
-    // late 913.
+    // late 913.  Out of place of 8192, whose copy fills the registers of <4, 1>: at 64 x 2^22
+    // samples <2, 2> 111 and <4, 1> 118, with bursts on 45% of them 200 and 268.
     const bool in_place = d_out == d_x;
     hipError_t e;
     if (block <= 2048) e = in_place ? go(launch_blank<1, 1, kInPlace>) : go(launch_blank<1, 1, kCopyLate>);
     else if (block <= 4096) e = in_place ? go(launch_blank<2, 1, kInPlace>) : go(launch_blank<2, 1, kCopyLate>);
-    else if (block <= 8192) e = in_place ? go(launch_blank<4, 1, kInPlace>) : go(launch_blank<4, 1, kCopyLate>);
+    else if (block <= 8192) e = in_place ? go(launch_blank<4, 1, kInPlace>) : go(launch_blank<2, 2, kCopyLate>);
     else if (block <= 12288 && in_place) e = go(launch_blank<6, 1, kInPlace>);
     else if (block <= 16384) e = in_place ? go(launch_blank<4, 2, kInPlace>) : go(launch_blank<4, 2, kCopyLate>);
     else if (block <= 24576 && in_place) e = go(launch_blank<6, 2, kInPlace>);
