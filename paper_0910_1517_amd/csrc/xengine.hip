@@ -645,11 +645,23 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
     // Data that are not finite are done on the FP32 instructions (below); most such data,
     // an antenna that is NaN throughout, show in the first chunk, which each thread
     // looks at where it has put it, before a step is lost on them.
-    __shared__ __attribute__((aligned(16))) uint32_t spoilt[2][kXWaves];
+    __shared__ __attribute__((aligned(16))) uint32_t spoilt[2][kXWaves], in_gate[GATED ? kXWaves : 1];
     auto not_finite = [](float x) __attribute__((always_inline)) { return __builtin_amdgcn_classf(x, 0x207); };
     stage(0, 0);
     load_keep(0);
     load_gate(0);
+    if constexpr (GATED) {
+        // The split's spectra of this gate.  A sum of four and fewer is more exact on the
+        // FP32 instructions, with two roundings a spectrum (one spectrum: 3.3e-8 rms of the
+        // pair's power and 1.2e-7 at most, here 3.8e-8 and 2.1e-7; four 3.2e-8 and 3.3e-8;
+        // 16 4.8e-8 and 3.3e-8).  Counting costs calls of four K-steps 4%, longer ones nothing.
+        const uint32_t *w = reinterpret_cast<const uint32_t *>(gate) + 4 * (int64_t)sp * steps;
+        uint32_t n = 0;
+        for (int e = i; e < 4 * steps; e += 64 * kXWaves)
+            n += (uint32_t)__builtin_popcount(eq_bytes(w[e], (uint32_t)bin * 0x01010101u)) / 8;
+        n = min(n, 7u);  // a wave's sum of these is enough
+        in_gate[wv] = __popcll(__ballot(n & 1)) + 2 * __popcll(__ballot(n & 2)) + 4 * __popcll(__ballot(n & 4));
+    }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     bool bad = false;
     if (cp) {
@@ -670,6 +682,13 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
         return __builtin_amdgcn_readfirstlane(c[0] | c[1] | c[2] | c[3]) != 0;
     };
     bool redo = told(0);
+    if constexpr (GATED) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int q = 0; q < kXWaves; ++q) n += in_gate[q];
+        n = __builtin_amdgcn_readfirstlane(n);
+        redo |= n >= 1 && n <= 4;
+    }
     if constexpr (NT == 2) {
         // The parts of row tile 0 are made a phase ahead of their use, and those of
         // tile 1 during the products of tile 0, so that vector and matrix
