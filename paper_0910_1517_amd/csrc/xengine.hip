@@ -432,9 +432,11 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
 // cell moves the last bits of the other seven): the bad pairs come out as those
 // instructions give them.  A dead antenna, NaN throughout, shows before the first
 // step and costs what it cost when every block ran on the FP32 instructions (64 x
-// 512 x 16384: 1510 us, 1490 then; two gates 2950 and 3540); found only at the end of
-// a block, by a fallback that spilled, it had cost 3600 us.  A bad cell elsewhere
-// costs its own block what both passes take, at most.
+// 512 x 16384: 1450 us, 1480 then; two gates 2910 and 3540; with flags that leave it in
+// and 33 to 48 signals 15% more).  Found only at the end of a block it had cost 3600 us,
+// also because that left the registers of the products and of the fallback's loads to
+// share: 49 to 62 a lane went through scratch memory.  A bad cell elsewhere costs its
+// own block what both passes take, at most.
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
@@ -458,8 +460,8 @@ __device__ __forceinline__ void split_pair(float x, float y, uint32_t (&p)[3]) {
 
 constexpr int kSplitChunks = 8;  // chunks of 2 spectra per K-step
 
-// A value that is the same in every lane, into scalar registers (the arguments of a
-// function call and the results of divisions come in vector registers).
+// A value that is the same in every lane, into scalar registers (the result of a
+// division comes in a vector register).
 template <typename T>
 __device__ __forceinline__ T uniform(T v) {
     union {
@@ -470,25 +472,6 @@ __device__ __forceinline__ T uniform(T v) {
 #pragma unroll
     for (int i = 0; i < (int)(sizeof(T) / 4); ++i) u.w[i] = __builtin_amdgcn_readfirstlane(u.w[i]);
     return u.v;
-}
-
-// The block on the FP32 instructions, a function of its own: inlined behind the
-// block below, whose registers are all in use, its prefetch went through scratch
-// memory with a wait for every load, and the registers of both went there too (49 to
-// 62 a lane; two gates at 64 x 512 x 16384 2260 us so, 1930 as a call).  Pointers have
-// their address space: generic ones would make every access a flat one, which waits
-// for LDS and memory alike.
-#define GLOBAL_ __attribute__((address_space(1)))
-#define LDS_ __attribute__((address_space(3)))
-template <int NT, bool GATED, bool MASKED>
-__device__ __attribute__((noinline)) void xengine_block_fp32(const GLOBAL_ uint8_t *spec, GLOBAL_ float *out, int S,
-                                                             int C, int T, int splits, int kb, int sp,
-                                                             LDS_ uint8_t *lds, const GLOBAL_ uint8_t *gate, int bin,
-                                                             const GLOBAL_ uint32_t *keep) {
-    xengine_block<NT, CORR_FP32, float, GATED, MASKED>(
-        (const uint8_t *)uniform(spec), (float *)uniform(out), uniform(S), uniform(C), uniform(T), uniform(splits),
-        uniform(kb), uniform(sp), (uint8_t *)uniform(lds), (const uint8_t *)uniform(gate), uniform(bin),
-        (const uint32_t *)uniform(keep));
 }
 
 // The block of xengine_block, for FP32 spectra.  A K-step is 16 spectra: lanes
@@ -511,7 +494,7 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
     static_assert(2 * kSplitChunks * blk <= x_lds_bytes<NT>(), "both buffers fit");
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = kXWaves * kb + wv;
     const int lane = threadIdx.x & 63, row = lane & 31, lg = lane >> 5;
-    const int steps = uniform(T / (2 * kSplitChunks) / splits);  // (a division leaves it in a vector register)
+    const int steps = uniform(T / (2 * kSplitChunks) / splits);
     const int64_t P = (int64_t)S * (S + 1) / 2;
     if (steps < 1) return;
 
@@ -527,8 +510,8 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
         if (cp) {
 #pragma unroll
             for (int j = 0; j < kSplitChunks; ++j)
-                __builtin_amdgcn_global_load_lds((const GLOBAL_ void *)(g + j * gstride), (LDS_ void *)(l + j * blk), 16, 0,
-                                                 0);
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(g + j * gstride),
+                                                 (__attribute__((address_space(3))) void *)(l + j * blk), 16, 0, 0);
         }
     };
     // keep bits of this lane's 8 spectra of a step, per row tile (shifted at once,
@@ -764,12 +747,7 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
 #pragma unroll
         for (int r = 0; r < 16; ++r) z = fmaf(acc[t][r], 0.f, z);
     if (redo || __syncthreads_or(z != z)) {
-        if constexpr (NT == 2)
-            xengine_block_fp32<NT, GATED, MASKED>((const GLOBAL_ uint8_t *)spec, (GLOBAL_ float *)out, S, C, T, splits, kb,
-                                                  sp, (LDS_ uint8_t *)lds, (const GLOBAL_ uint8_t *)gate, bin,
-                                                  (const GLOBAL_ uint32_t *)keep);
-        else  // (the registers suffice; a call would take half of a compute unit's workgroups)
-            xengine_block<NT, CORR_FP32, float, GATED, MASKED>(spec, out, S, C, T, splits, kb, sp, lds, gate, bin, keep);
+        xengine_block<NT, CORR_FP32, float, GATED, MASKED>(spec, out, S, C, T, splits, kb, sp, lds, gate, bin, keep);
         return;
     }
     v16f accR[ntri(NT)], accM[NT * NT];
