@@ -64,7 +64,7 @@ typedef int32_t corr_status;
 #define CORR_ERR_IO (-11)         /* file could not be opened, read or written  */
 
 /* Arithmetic of the spectra handed from the F- to the X-engine. */
-#define CORR_FP32 0     /* complex64 spectra, FP32-accurate BF16 MFMA X-engine   */
+#define CORR_FP32 0     /* complex64 spectra, FP32-accurate X-engine (below)     */
 #define CORR_INT8 1     /* int8 (re, im) in [-127, 127], int8 MFMA, int32 sums  */
 #define CORR_FP8_E4M3 2 /* OCP e4m3 (re, im), FP8 MFMA, FP32 sums               */
 
@@ -264,6 +264,14 @@ corr_status corr_requantize(corr_plan_t *plan, const float *d_in, const float *d
  *            every cell.  4-byte aligned.
  *   d_acc    corr_plan_acc_bytes, 256-byte aligned, zeroed once before the
  *            first call (corr_integrate zeroes it afterwards).
+ * FP32: products are exact to FP32's 2^-24, and a sum's error is no more than that
+ * of FP32 products added one after the other (from about 8 spectra on it is
+ * smaller; where flags leave a pair one to four spectra it may reach 2^-22 of
+ * the pair's power).  That holds for components that are zero or at least 2^-110
+ * in magnitude; smaller ones lose their bits below 2^-133, which can show only
+ * in products with very large ones.  A cell that is not finite (and not flagged)
+ * spoils its own signal's pairs of its channel; the other sums of its block of 8
+ * channels may round differently than without it.
  *   d_counts optional (needs d_keep and the bound workspace): += the exact
  *            per-pair unflagged counts, as corr_pair_counts (int32 [C][P]),
  *            4-byte aligned.

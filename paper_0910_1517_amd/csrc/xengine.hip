@@ -425,12 +425,14 @@ __device__ __forceinline__ void xengine_block(const uint8_t *__restrict__ spec, 
 // 1.70 ms there, now 1.06 ms (4.1 TB/s; its loads alone 0.83 ms, its arithmetic
 // alone 0.88 ms at the 1.7 GHz this load leaves the clock).
 //
-// Values of 2^-100 and more in magnitude (and zeros) split exactly.  A value
-// that is infinite or NaN, or within half a BF16 step of the largest FP32
-// number, leaves a NaN in every sum it takes part in; a block with a sum that is
-// not finite is done on the FP32 instructions instead, all its 8 channels (so a bad
-// cell moves the last bits of the other seven): the bad pairs come out as those
-// instructions give them.  A dead antenna, NaN throughout, shows before the first
+// Values of 2^-110 and more in magnitude (and zeros) split exactly: the matrix
+// cores take subnormal BF16 numbers, down to 2^-133, and keep subnormal products
+// (amplitudes of 2^-62 to 2^58 have the same errors).  A value that is infinite or
+// NaN, or within half a BF16 step of the largest FP32 number, leaves a NaN in every
+// sum it takes part in; a block with a sum that is not finite is done on the FP32
+// instructions instead, all its 8 channels (so a bad cell moves the last bits of the
+// other seven): the bad pairs come out as those instructions give them.  A dead
+// antenna, NaN throughout, shows before the first
 // step and costs what it cost when every block ran on the FP32 instructions (64 x
 // 512 x 16384: 1450 us, 1480 then; two gates 2910 and 3540; with flags that leave it in
 // and 33 to 48 signals 15% more).  Found only at the end of a block it had cost 3600 us,
