@@ -224,7 +224,10 @@ corr_status corr_plan_bind_workspace(corr_plan_t *plan, void *d_ws, size_t bytes
  *              power_fp16 FP16 |X|^2 / N^2 (the FP32 value times the exact
  *              power of two, rounded to nearest even); X before phase
  *              rotation and requantisation (the rotation keeps |X|).  4-byte
- *              (FP32) or 2-byte (FP16) aligned.
+ *              (FP32) or 2-byte (FP16) aligned.  Asking for it does not change
+ *              the spectra, but for FP32 ones of 512 channels (fft_len 1024,
+ *              phase_lut 0): with and without d_power these come from two
+ *              kernels of the same accuracy that round differently.
  * Errors: NULL, ALIGN, INVALID (row_stride), WORKSPACE, DEVICE.
  */
 corr_status corr_fengine(corr_plan_t *plan, const int8_t *d_x, int64_t row_stride,
