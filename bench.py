@@ -57,13 +57,13 @@ MEASURED_TRAFFIC = {
     # profiles/fx_int8_64sig_4096pt_32768spec.md: FETCH_SIZE 4471217 KiB x 2.000, WRITE_SIZE 8388671 KiB x 1.000
     # (medians of 9 dispatches, with the source's instruction-level-parallelism schedule)
     "fengine_int8_c3": {"source": "paper_0910_1517_amd/csrc/fengine4.hip",
-                        "sha256": "ea1e5adf8c00e3dc987735b3db58ae458b567cd3d8fb5ecf0376f32bb6586bfb",
+                        "sha256": "8319df21a31c0fbbdda7757fe2cfa6fef60746bf1c9c55a4d993d8cd67678962",
                         "flags": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-sched-strategy=max-ilp"],
                         "read": 9.157e9, "write": 8.590e9},
     # profiles/fx_fp32_64sig_1024pt_16384spec_pointsources.md: FETCH_SIZE 531970 KiB x 2.000, WRITE_SIZE 4337386 KiB
     # (medians of 6 dispatches)
     "fengine_fp32_c2": {"source": "paper_0910_1517_amd/csrc/fengine4.hip",
-                        "sha256": "ea1e5adf8c00e3dc987735b3db58ae458b567cd3d8fb5ecf0376f32bb6586bfb",
+                        "sha256": "8319df21a31c0fbbdda7757fe2cfa6fef60746bf1c9c55a4d993d8cd67678962",
                         "flags": ["-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-amdgpu-sched-strategy=max-ilp"],
                         "read": 1.089e9, "write": 4.441e9},
     # profiles/cnn_flagged_64sig_8192pt_8192spec.md (FP16 power, column guard, max-ilp schedule): FETCH_SIZE

@@ -74,19 +74,18 @@ struct F4Cfg {
     static constexpr int LOGN1 = LOGM - 5;
     static constexpr int L = M / 8;         // threads per window (4 N1)
     static constexpr int FPAR = (L >= 256) ? 1 : 256 / L;
-    static constexpr int WG = L * FPAR;     // 256, 512 or 1024
+    static constexpr int WG = L * FPAR;     // 256 at the lengths built (the kernel asserts it)
     static constexpr int J = WG / 32;       // threads per column (over all windows)
     static constexpr int BPC = N1 / 8;      // radix-8 butterflies per column
     static constexpr int NP8 = LOGN1 / 3;
     static constexpr int RLAST = 1 << (LOGN1 % 3);
     static constexpr int NPASS = NP8 + (RLAST > 1 ? 1 : 0);
-    // stride (float2) of the columns (elements at swz) and of the window slots: the LDS serves 16 lanes of an 8-byte access in a cycle, over 32
-    // banks, and these put the 16 -- 8 columns, 2 butterflies or slots -- on
-    // distinct ones
+    // stride (float2) of the columns (elements at swz) and of the window slots: the LDS
+    // serves 16 lanes of an 8-byte access in a cycle, over 32 banks, and these put the
+    // 16 -- 8 columns, 2 butterflies or slots -- on distinct ones
     static constexpr int CS = N1 == 8 ? 9 : N1 + 2;
     static constexpr int SS = 32 * CS + (N1 == 8 ? 8 : 0);
     static_assert(N1 == 8 || N1 == 16 || N1 == 32 || N1 == 64, "strides for these lengths");
-    static constexpr int NBUF = 1;          // column passes run in place
     static constexpr int AP = 72;           // LDS row pitch (FP16) of the DFT-64 rows
     static constexpr int NSPEC = WG / 4;    // channels of column 0 per iteration (FPAR N1)
     static constexpr int SPS = 32;          // most spectra per window slot
@@ -174,13 +173,12 @@ constexpr int twl_count(int logn) {
     return n;
 }
 
-// One radix-R Stockham pass PS over a column of N1 points: butterfly i reads
-// src[i + r N1/R], multiplies by W_(P R)^(r k) (k = i mod P; the contiguous
-// table entries [k][r] of this pass), transforms and writes dst[(i - k) R + k +
+// One radix-R Stockham pass PS over a column of N1 points, in place: butterfly i
+// reads z[i + r N1/R], multiplies by W_(P R)^(r k) (k = i mod P; the contiguous
+// table entries [k][r] of this pass), transforms and writes z[(i - k) R + k +
 // q P].  The last pass returns its outputs, k1 = i + q N1/R, in v.
 template <int LOGM, int PS>
-__device__ __forceinline__ void col_pass(const float2 *src, float2 *dst, const float2 *twp, int b,
-                                         float2 (&v)[8]) {
+__device__ __forceinline__ void col_pass(float2 *z, const float2 *twp, int b, float2 (&v)[8]) {
     using C = F4Cfg<LOGM>;
     constexpr int R = pass_radix(C::LOGN1, PS);
     constexpr int P = 1 << (3 * PS);
@@ -190,9 +188,9 @@ __device__ __forceinline__ void col_pass(const float2 *src, float2 *dst, const f
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
 #pragma unroll
-        for (int r = 0; r < R; ++r) v[u * R + r] = src[swz(b + BPC * u + r * (N1 / R))];
+        for (int r = 0; r < R; ++r) v[u * R + r] = z[swz(b + BPC * u + r * (N1 / R))];
     }
-    if constexpr (C::NBUF == 1 && !LAST) __syncthreads();  // in place: every read before any write
+    if constexpr (!LAST) __syncthreads();  // every read before any write
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
         if constexpr (PS > 0) {
@@ -217,21 +215,17 @@ __device__ __forceinline__ void col_pass(const float2 *src, float2 *dst, const f
             const int k = i & (P - 1);
             const int j = (i - k) * R + k;
 #pragma unroll
-            for (int q = 0; q < R; ++q) dst[swz(j + q * P)] = v[u * R + q];
+            for (int q = 0; q < R; ++q) z[swz(j + q * P)] = v[u * R + q];
         }
     }
 }
 
 template <int LOGM, int PS>
-__device__ __forceinline__ void col_passes(float2 *b0, float2 *b1, const float2 *twp, int colo, int b,
-                                           float2 (&v)[8]) {
-    using C = F4Cfg<LOGM>;
-    if constexpr (PS < C::NPASS) {
+__device__ __forceinline__ void col_passes(float2 *z, const float2 *twp, int b, float2 (&v)[8]) {
+    if constexpr (PS < F4Cfg<LOGM>::NPASS) {
         if (PS > 0) __syncthreads();
-        float2 *src = (C::NBUF == 1 || (PS & 1) == 0) ? b0 : b1;
-        float2 *dst = (C::NBUF == 1 || (PS & 1) == 1) ? b0 : b1;
-        col_pass<LOGM, PS>(src + colo, dst + colo, twp, b, v);
-        col_passes<LOGM, PS + 1>(b0, b1, twp, colo, b, v);
+        col_pass<LOGM, PS>(z, twp, b, v);
+        col_passes<LOGM, PS + 1>(z, twp, b, v);
     }
 }
 
@@ -255,7 +249,8 @@ struct Chan {
 };
 
 // Phase, requantisation and corner turn of a channel's value X in spectrum r of
-// the slot; the caller stores finished chunks.  FP32: H = 0 the even spectrum of the pair, H = 1 the odd one.
+// the slot; the caller stores finished chunks.  FP32: H = 0 the even spectrum of
+// the pair, H = 1 the odd one.
 // INT8 / FP8: the codes go into byte r mod 4 of a pair of words.  H = 0 or 1
 // (the caller knows which half of the chunk spectrum r is in): the first
 // (spectra 0..3 of the chunk) or second (4..7) pair.  H = -1: the second pair,
@@ -318,7 +313,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     __shared__ __attribute__((aligned(16))) uint32_t lds_x[H16 ? 1 : 2][FPAR][H16 ? 4 : N / 4];
     __shared__ __attribute__((aligned(16))) _Float16 lds_xh[H16 ? FPAR : 1][H16 ? (N / N1) * XP : 8];
     __shared__ __attribute__((aligned(16))) float2 lds_tw[twl_count(C::LOGN1) > 0 ? twl_count(C::LOGN1) : 1];
-    __shared__ __attribute__((aligned(16))) float2 lds_b[C::NBUF][FPAR * C::SS];
+    __shared__ __attribute__((aligned(16))) float2 lds_b[FPAR * C::SS];
     __shared__ __attribute__((aligned(16))) uint16_t lds_a[2][64 * C::AP];  // FP16 rows (hi, lo)
     __shared__ __attribute__((aligned(16))) float2 lds_u[FPAR * N1];  // column 0 outputs
     __shared__ float2 lds_rot[SPB_MAX];
@@ -465,8 +460,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     };
     fetch(m_fetch);
 
-    float2 *lb0 = &lds_b[0][0];
-    float2 *lb1 = &lds_b[C::NBUF - 1][0];
+    float2 *cols = lds_b;
     // spectra of the thread's column slot and of its column-0 channel
     const int m_c0 = mblk + sps * bu, m_s0 = mblk + sps * nspec_u;
     const bool c_active = m_c0 < a.T, s_active = m_s0 < a.T;
@@ -522,7 +516,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
     // 1190 so (without cells 903); FP32 with FP32 cells 2284 and 1692 (1283).
     // Cell k1 of column cp of window slot u; column 0 holds the channels 32 j at j.
     // The skews spread a wave's writes and its reads over the banks.
-    float *const lp = reinterpret_cast<float *>(lb0);
+    float *const lp = reinterpret_cast<float *>(cols);
     auto cell = [&](int u, int cp, int k1) -> int {
         const int skew = N1 == 64 ? cp >> 3 : N1 == 32 ? 4 * u + (cp >> 3) : u >> 2;
         return 2 * (u * C::SS + cp * C::CS) + skew + k1;
@@ -642,12 +636,12 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
             const int p = 16 * mt + 4 * (v >> 2) + 2 * hh + ((v & 3) >> 1);
             const float2 A = make_float2(acc[v], acc[v + 1]);
             if (v == 0 && mt == 0 && hh == 0) {
-                float *u0 = reinterpret_cast<float *>(lb0 + au * C::SS);
+                float *u0 = reinterpret_cast<float *>(cols + au * C::SS);
                 const float y0 = 0.5f * (A.x + A.y), y1 = 0.5f * (A.x - A.y);
                 u0[2 * swz(an1 >> 1) + (an1 & 1)] = y0;
                 u0[2 * swz((an1 >> 1) + N1 / 2) + (an1 & 1)] = y1;
             } else {
-                lb0[au * C::SS + p * C::CS + swz(an1)] = cmul(A, tws[v >> 1]);
+                cols[au * C::SS + p * C::CS + swz(an1)] = cmul(A, tws[v >> 1]);
             }
         }
         flush3(3);
@@ -655,7 +649,7 @@ __global__ void __launch_bounds__(F4Cfg<LOGM>::WG) __attribute__((amdgpu_waves_p
         __syncthreads();
         flush3(6);
         float2 z[8];
-        col_passes<LOGM, 0>(lb0, lb1, lds_tw, colo, bb, z);
+        col_passes<LOGM, 0>(cols + colo, lds_tw, bb, z);
         if (cp == 0) {
 #pragma unroll
             for (int o = 0; o < 8; ++o) {
