@@ -69,7 +69,7 @@ MEASURED_TRAFFIC = {
     # profiles/cnn_flagged_64sig_8192pt_8192spec.md (FP16 power, column guard, max-ilp schedule): FETCH_SIZE
     # 2097369 KiB x 2.000, WRITE_SIZE 2097152 KiB
     "cnn_infer_c5": {"source": "paper_0910_1517_amd/csrc/cnn.hip",
-                     "sha256": "7b19ceae8122231127e27017344549a5f359ab2c6d2af835642800ff532689a8",
+                     "sha256": "0fd875ae69e8aecfdcf9af0a9511eb1f0c166302412f718456535dfd4301bd83",
                      "flags": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
                      "read": 4.295e9, "write": 2.147e9},
     # profiles/fx_int8_64sig_4096pt_32768spec.md: FETCH_SIZE 4197483 KiB x 2.000, WRITE_SIZE 1572864 KiB x 1.000

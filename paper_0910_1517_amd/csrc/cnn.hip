@@ -604,12 +604,12 @@ __device__ inline int a1_off(int pcol, int h) { return 32 * pcol + 16 * (h ^ (((
 //   the logits of rows 2j - 6, 2j - 5,
 // mostly vector instructions and LDS accesses, the other
 //   layer 2 and the layer-3 tap sums for rows 2j - 2, 2j - 1,
-// mostly matrix products, which so run beside the first: a wave that took all
-// the stages in turn had every unit waiting for another (matrix cores, vector ALUs
-// and LDS each busy 42%; 64 x 4096 x 4096 FP16 cells with 8 such waves 8030 us,
-// now 7280).  The layer-2 waves have the higher priority (4% slower without): their
-// step is the longer one.
-// each stage reading only what earlier steps wrote, from rings of 8 rows.
+// mostly matrix products, which so run beside the first, each stage reading only
+// what earlier steps wrote, from rings of 8 rows.  A wave that took all the stages in
+// turn had every unit waiting for another (matrix cores, vector ALUs and LDS each
+// busy 42%; 64 x 4096 x 4096 FP16 cells with 8 such waves 8030 us, now 7280).  The
+// layer-2 waves have the higher priority (4% slower without): their step is the
+// longer one.
 // Layer 2 of a row pair reads layer-1 rows 2j - 3 .. 2j; the first two were
 // read by the previous step and stay in registers.  Layer-1 rows -1 and 64
 // are zero rows in the ring.  Steps run four at a time (the ring period), so
@@ -780,8 +780,8 @@ __global__ void __launch_bounds__(IWG) cnn_infer_kernel(const float *__restrict_
     };
     // First tile: column sums of rows xh, xh + 2, ... and the input rows -1 + xh,
     // 1 + xh, 3 + xh of its first steps.  Later tiles get these during the previous one.
-    // Offsets inside a tile (row r, column c: r C + c < 2^24) are 32-bit;
-    // tile bases are uniform 64-bit pointers.
+    // Offsets inside a tile (row r < 2^6, column c, C up to 2^22: operands of 24 bits,
+    // r C + c < 2^29) are 32-bit; tile bases are uniform 64-bit pointers.
     auto roff = [&](int r, int c) { return __umul24((uint32_t)r, (uint32_t)C) + (uint32_t)c; };
     int tile = blockIdx.x;
     // p0, p1: input rows -1 + xh, 1 + xh of a tile; p2 .. p5: rows 3 + xh ..
