@@ -146,8 +146,10 @@ constexpr int kLutSteps = 1440;
 // workgroups a compute unit gets, `per_cu` side by side, each costing its slot
 // plus a set-up of `setup` spectra; a last group that is not full runs its
 // fewer workgroups faster, but not in proportion (one of two workgroups alone:
-// 0.78 of the pair's time).  It picks within 3% of the fastest of all slots for
-// 28 measured shapes (4..64 signals, 512..16384 points, 64..4096 spectra).
+// 0.78 of the pair's time).  Of 186 shapes (FP32 and int8 spectra, 4..64 signals,
+// 512..16384 points, 64..4096 spectra) it picks within 3% of the fastest of all slots
+// for 153, within 5% for 177 and within 9% for all but one (FP32, 4 x 4096 x 4096: 114 us,
+// 102 with 32 spectra); FP32 spectra of 8192 points would be 5 to 9% faster at 2.
 inline int fengine_spectra(int S, int T, int fpar, int most, int least, int per_cu, double setup) {
     constexpr int kCus = 256;
     int best = most;

@@ -132,7 +132,8 @@ constexpr int twiddle_offset(int logm, int ps) {
 // compiler only has to keep them so, and the waves of a workgroup, which share
 // nothing, need not wait for each other (64 x 512 x 16384: int8 1190 -> 1135 us,
 // e4m3 1200 -> 1136).  FP32 output keeps the workgroup barriers: its writes, four
-// times as many, go out better in step (1705 us with, 1785 and more without).
+// times as many, go out better in step (with FP32 power cells 2039 us with them, 2312
+// without; with the phase table 1939 and 2036, at 64 x 256 x 32768 1862 and 1968).
 template <int LOGM, int BM>
 __device__ __forceinline__ void transform_sync() {
     if constexpr (FCfg<LOGM>::L <= 64 && BM != 0) {
