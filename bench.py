@@ -72,17 +72,17 @@ MEASURED_TRAFFIC = {
                      "sha256": "0fd875ae69e8aecfdcf9af0a9511eb1f0c166302412f718456535dfd4301bd83",
                      "flags": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
                      "read": 4.295e9, "write": 2.147e9},
-    # profiles/fx_int8_64sig_4096pt_32768spec.md: FETCH_SIZE 4197483 KiB x 2.000, WRITE_SIZE 1572864 KiB x 1.000
+    # profiles/fx_int8_64sig_4096pt_32768spec.md: FETCH_SIZE 4197634 KiB x 2.000, WRITE_SIZE 1572864 KiB x 1.000
     "beam_int8_c3": {"source": "paper_0910_1517_amd/csrc/beam.hip",
-                     "sha256": "fdea2c6b6d608a65e64c732609303dc9d4f9377b18ad830e8b407f4c35843b4f",
+                     "sha256": "d179613b3e0691769814b9c0d916337596cd4319454411b2a5fb214641e6ce20",
                      "read": 8.597e9, "write": 1.611e9},
-    # profiles/blank_int8_64sig_134Msamples.md: out of place FETCH_SIZE 4211137 KiB x 2.000, WRITE_SIZE 8520888 KiB
+    # profiles/blank_int8_64sig_134Msamples.md: out of place FETCH_SIZE 4211110 KiB x 2.000, WRITE_SIZE 8557230 KiB
     "blank_out_c3": {"source": "paper_0910_1517_amd/csrc/blank.hip",
-                     "sha256": "0f09cbd71dbe95a51c5f6e8a2c92a094a331ac9e00aaf0e0b11e760ee0127ff8",
-                     "read": 8.624e9, "write": 8.725e9},
-    # same profile, in place: FETCH_SIZE 4211154 KiB x 2.000, WRITE_SIZE 900717 KiB
+                     "sha256": "ed38856f064c6ed19784e1dae55a2abfafe08255cdbbd7b9f525dc2764cd49da",
+                     "read": 8.624e9, "write": 8.763e9},
+    # same profile, in place: FETCH_SIZE 4211062 KiB x 2.000, WRITE_SIZE 900715 KiB
     "blank_in_c3": {"source": "paper_0910_1517_amd/csrc/blank.hip",
-                    "sha256": "0f09cbd71dbe95a51c5f6e8a2c92a094a331ac9e00aaf0e0b11e760ee0127ff8",
+                    "sha256": "ed38856f064c6ed19784e1dae55a2abfafe08255cdbbd7b9f525dc2764cd49da",
                     "read": 8.624e9, "write": 0.922e9},
 }
 
@@ -861,7 +861,7 @@ def main():
                              "traffic": measured_traffic("beam_int8_%s" % args.config)}
         gbs = rb["bytes_out_of_place"] / rb["ms_out_of_place"] / 1e6
         out["voltage_blanker"] = {
-            "kernel": "blank_kernel<4> (MAD blanker, blocks of 16384 samples)", "bound": "hbm",
+            "kernel": "blank_kernel<4, 2, 2> (MAD blanker, blocks of 16384 samples; in place <4, 2, 0>)", "bound": "hbm",
             "input": "the int8 input rows with impulsive bursts added to about 2.5 % of the samples",
             "blanked_fraction": round(rb["blanked_fraction"], 5),
             "ms_out_of_place": round(rb["ms_out_of_place"], 4), "achieved_gbs": round(gbs, 1),
