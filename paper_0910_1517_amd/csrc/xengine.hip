@@ -998,7 +998,8 @@ hipError_t launch_xengine_gated(int precision, const void *spec, const uint8_t *
     // pair costs a workgroup: five bins of 4 x 2048 x 64 22.4 and 17.8 us, of 64 x 8192 x 256
     // 571 and 564, three of 64 x 2048 x 8192 1090 and 990.  With one signal tile it still pays
     // off for more than 20 signals (five bins of 32 x 2048 x 512: 14% faster in pairs; of 24
-    // signals 4%; of 20, 2% slower) or from nine bins of eight steps on (4 x 2048 x 512: 4%; of four steps 5% slower).
+    // signals 4%; of 20, 2% slower) or from nine bins of eight steps on (4 x 2048 x 512: 4%;
+    // of four steps 5% slower).
     const bool two = S > 32;
     const int steps = T / 32 / splits;  // of 8-bit codes
     const bool odd = !two && n_bins > 3 && (S > 20 || (n_bins >= 9 && steps >= 8));
