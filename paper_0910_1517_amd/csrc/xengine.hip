@@ -725,7 +725,7 @@ __device__ __forceinline__ void xengine_block_split(const uint8_t *__restrict__ 
                 load_gate(clamped(st + 1));
             }
             redo = told(turn);
-            spoilt[turn ^ 1][wv] = __any(not_finite(acc[0][0]) | not_finite(acc[2][0]));
+            spoilt[turn ^ 1][wv] = __any(not_finite(acc[0][0]) || not_finite(acc[2][0]));
         }
         arrived();
     } else {
